@@ -245,12 +245,21 @@ sdq_status sdq_quantize_compensated(const float* w_dev, const sdq_layout* layout
  *                 base-3 codes in the order of their digits: per group of
  *                 four 80-code chunks, five 64-code steps), then the fp32
  *                 plane scale of every (row, block);
- *   m > 16:       fp16 x_tilde, m x k_up rounded up to whole chunks (twice,
- *                 an fp16 pair hi + lo, for layouts with SDQ_HAD_NONE), each
- *                 row scaled by a power of two p_i that keeps it inside
- *                 fp16's normal range, then p_i and 1 / p_i (fp32 [m] each);
+ *   m > 16:       x_tilde as three FP6 digit planes with a power-of-two scale
+ *                 per 32 samples (m rounded up to 32 rows, k_up to 256
+ *                 samples, 73 bytes per 32 samples), the row factors below,
+ *                 and the partial sums of a contraction split over K; or,
+ *                 for layouts with SDQ_HAD_NONE, an fp16 pair hi + lo of
+ *                 m x k_up (rounded up to whole chunks) each, every row scaled
+ *                 by a power of two p_i that keeps it inside fp16's normal
+ *                 range, then p_i and 1 / p_i (fp32 [m] each);
  * for a base-3 layout and m > 16 the chunks are those of 2-bit fields, and the
- * 2-bit copy of the codes follows (n_pad x ceil(k_up / 64) x 16 bytes). */
+ * 2-bit copy of the codes follows x_tilde (n_pad x ceil(k_up / 64) x 16 bytes).
+ * Calls with m > 16 also accept less: from the size of one fp16 x_tilde with its
+ * row factors (and the 2-bit copy) on, a call takes the fastest form that fits
+ * (fewer splits, then fp16 x_tilde; results differ within the stated accuracy).
+ * An expansion and the contractions that read it must be given the same
+ * workspace size. */
 size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
 
 /*
@@ -269,8 +278,9 @@ size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
  *                fp32) quantised to 24-bit fixed point and an exact int8 x
  *                int8 -> int32 matrix-core contraction against the codes
  *                (each code a +-1 or 0 weight: the products select, negate
- *                or drop the activations); larger m: the prefill path (fp16
- *                expansion, fp16 matrix cores).
+ *                or drop the activations); larger m: the prefill path (digit
+ *                planes on the FP6 x FP4 matrix cores, or fp16; see
+ *                sdq_linear_workspace_bytes).
  *   codes_dev, scales_dev  as written by sdq_quantize for `layout`.
  *   y_dev        fp32 [m x n] output, row-major.
  *   accumulate   0: y = x W_hat^T (y fully overwritten);  nonzero: y += x W_hat^T
@@ -281,7 +291,7 @@ size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
  * fp64 definition.  The decode path splits K across workgroups for large
  * layers and then adds the partial sums into y with fp32 atomics, so results
  * may differ between calls in the last bits (relative ~1e-6); the prefill path
- * and unsplit decodes are bitwise deterministic.  Calls that share a
+ * and unsplit decodes are bitwise deterministic (for one workspace size).  Calls that share a
  * workspace must be ordered (same stream).
  * Errors: SDQ_ERR_ARG, SDQ_ERR_SHAPE, SDQ_ERR_WORKSPACE, SDQ_ERR_NOMEM, SDQ_ERR_HIP. */
 sdq_status sdq_linear(const void* x_dev, sdq_dtype xt, int64_t m, const void* codes_dev,
@@ -328,7 +338,7 @@ sdq_status sdq_linear_group_expanded(int64_t m, int32_t count, const void* const
  * errors as sdq_linear; the workspace is a fixed device array of
  * SDQ_NOALLOC_SCRATCH_BYTES inside the library, one per GPU, held until the
  * process ends (its address is looked up on the first call on each device).
- *  - Calls needing more workspace than that (sdq_linear_workspace_bytes)
+ *  - Calls that do not fit (the least size that sdq_linear accepts)
  *    return SDQ_ERR_WORKSPACE; they fit for every one-to-sixteen-row call on
  *    2-bit fields up to k = 28672 at OSR 8, and prefill while
  *    m * k_up * 2 bytes (twice that without Had) plus 8 m bytes of row

@@ -22,6 +22,7 @@ LIB = os.path.join(HERE, "libsdq.so")
 ARCH = os.environ.get("SDQ_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["sdq_api.cpp", "encoder.hip", "linear_decode.hip", "linear_prefill.hip", "expand_prefill.hip",
+           "prefill_digits.hip",
            "moments.hip", "compensation.hip", "linear_noalloc.hip"]
 
 COMMON = [
@@ -37,6 +38,7 @@ PER_FILE = {
     # AGPR copies, 64 moves and a pipeline drain per k step).
     "compensation.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "expand_prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "prefill_digits.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     # the 2-16-row contractions: without it the integer accumulators rotate
     # through AGPR copies, 40 moves per 64-code chunk at 5-8 rows
     "linear_decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

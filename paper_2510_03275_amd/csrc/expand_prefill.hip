@@ -8,7 +8,16 @@
 //            to fp16 (without Had also kept as an fp16 pair, the GEMM then
 //            running over both halves).
 //
-//   scale    fp16 holds normal numbers from 2^-14 to 65504 only, so every
+//   digits   Layouts with Had: every 32 consecutive samples of a row share a
+//            power of two 2^E (their largest magnitude is in [2, 4) 2^E) and
+//            are written as three FP6 digit planes for the contraction of
+//            prefill_digits.hip (15 bits of fixed point per 32 samples, so the
+//            rounding error is below that of one fp16 rounding: rms 5e-5
+//            against 2e-4 of Gaussian samples).  E takes the whole fp32 range,
+//            so no row factor is needed, and a block with a non-finite sample
+//            gets the scale NaN.
+//
+//   scale    fp16 x_tilde only (and the fp16 copies of fp32 x): fp16 holds normal numbers from 2^-14 to 65504 only, so every
 //            activation row i is first multiplied by a power of two p_i
 //            (exact) picked from its largest magnitude a_i:
 //            a_i max(e1max, 1) p_i < 2^14.  Each x_tilde sample of the row,
@@ -28,8 +37,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
-#include <string>
 #include <type_traits>
 #include <hip/hip_fp16.h>
 #include <hip/hip_bf16.h>
@@ -55,6 +62,108 @@ __device__ inline int64_t xcd_tile(int64_t id, int64_t n) {
   const int64_t xcd = id % kXcds, j = id / kXcds;
   const int64_t per = n / kXcds, rem = n % kXcds;
   return xcd * per + (xcd < rem ? xcd : rem) + j;
+}
+
+// ---------------------------------------------------------------------------
+// Digit planes.  Value v of a block with scale 2^E, u = v 2^-E in (-4, 4):
+//   d0 = u rounded to a multiple of 1/4          (|d0| <= 4)
+//   d1 = u - d0 rounded to a multiple of 2^-7    (|32 d1| <= 4)
+//   d2 = u - d0 - d1, times 1024 rounded to FP6  (|1024 d2| <= 4)
+// FP6 (e2m3) holds every multiple of 1/4 up to 4, so d0 and 32 d1 are exact and
+// u is represented to 2^-13 at most.  The roundings are additions of a power
+// of two and a half (six VALU instructions per sample; digits by integer
+// shifts and masks took about forty).
+typedef float floatx2x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x6 __attribute__((ext_vector_type(6)));
+
+// 32 floats to 32 FP6 values of 1 / scale (element 2 i from a[i], 2 i + 1 from
+// b[i]), rounded to nearest even.  The hardware writes the first result
+// registers before it has read the last operands, which the builtin's register
+// constraints do not say: hence the early clobber.
+__device__ inline u32x6 cvt_fp6(const floatx2x16& a, const floatx2x16& b, float scale) {
+  u32x6 r;
+  asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3\n\ts_nop 1" : "=&v"(r) : "v"(a), "v"(b), "s"(scale));
+  return r;
+}
+
+// The sample (of a block of 32) that K slot j of a digit plane holds: the order
+// in which the contraction expands the packed codes.  Ternary: dword d = j / 8
+// of the FP4 operand takes the even (d even) or odd codes of word d / 2.
+// Binary: dword d takes the codes 4 i + d.
+template <int LEVELS>
+constexpr int digit_sample(int j) {
+  return LEVELS == 3 ? 16 * (j / 16) + 2 * (j % 8) + (j / 8) % 2 : 4 * (j % 8) + j / 8;
+}
+
+// One lane: the 32 samples of one row's block, A[v] = sample 8 (v / 4) + v % 4
+// and Bv[v] = sample 8 (v / 4) + 4 + v % 4, to the digit planes of 32-block kb
+// of row `row` (kb in samples / 32 over the row).  zero_to: the 32-blocks kb +
+// 1 .. zero_to - 1 past the row's end are written as zeros.
+template <int LEVELS>
+__device__ inline void store_digits(const floatx16& A, const floatx16& Bv, int64_t row, int64_t n_rg, int64_t kb,
+                                    int64_t zero_to, uint8_t* __restrict__ planes) {
+  float mx = 0.0f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v)   // IEEE maximum: a NaN stays
+    mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, fabsf(A[v])), fabsf(Bv[v]));
+  const uint32_t mb = __float_as_uint(mx) & 0x7FFFFFFFu;
+  const uint32_t eb = mb >= 0x00800000u ? (mb >> 23) - 1u : 0u;      // E + 127
+  const float inv = __uint_as_float((254u - min(eb, 253u)) << 23);   // 2^-E
+  constexpr float M0 = 3145728.0f;             // 1.5 x 2^21: sums are multiples of 1/4
+  constexpr float M1 = 98304.0f;               // 1.5 x 2^16: multiples of 2^-7
+  floatx2x16 p0[2], p1[2], p2[2];
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const int smp = digit_sample<LEVELS>(j), v = 4 * (smp / 8) + smp % 4;
+    const float f = (smp & 4) ? Bv[v] : A[v];
+    const float d0 = __builtin_fmaf(f, inv, M0) - M0;
+    const float r = __builtin_fmaf(f, inv, -d0);
+    const float d1 = (r + M1) - M1;
+    p0[j % 2][j / 2] = d0;
+    p1[j % 2][j / 2] = d1;
+    p2[j % 2][j / 2] = r - d1;
+  }
+  const u32x6 q[3] = {cvt_fp6(p0[0], p0[1], 1.0f), cvt_fp6(p1[0], p1[1], 0.03125f),
+                      cvt_fp6(p2[0], p2[1], 0.0009765625f)};
+  if (row / 32 >= n_rg) return;
+  const int r32 = static_cast<int>(row % 32);
+  auto slot = [&](int64_t b32, int64_t* tile) {     // 32-block b32 of the row: its step and K half
+    const int64_t step = LEVELS == 3 ? b32 / 2 : 2 * (b32 / 4) + b32 % 2;
+    *tile = step * n_rg + row / 32;
+    return r32 + 32 * static_cast<int>(LEVELS == 3 ? b32 % 2 : (b32 / 2) % 2);
+  };
+  int64_t t;
+  const int ln = slot(kb, &t);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint8_t* dst = planes + t * kDigitTile + p * kDigitPlane;
+    *reinterpret_cast<uint4*>(dst + 16 * ln) = make_uint4(q[p][0], q[p][1], q[p][2], q[p][3]);
+    *reinterpret_cast<uint2*>(dst + 1024 + 8 * ln) = make_uint2(q[p][4], q[p][5]);
+  }
+  planes[t * kDigitTile + 3 * kDigitPlane + ln] = static_cast<uint8_t>(mb >= 0x7F800000u ? 255u : eb);
+  for (int64_t z = kb + 1; z < zero_to; ++z) {
+    const int lz = slot(z, &t);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      uint8_t* dst = planes + t * kDigitTile + p * kDigitPlane;
+      *reinterpret_cast<uint4*>(dst + 16 * lz) = make_uint4(0u, 0u, 0u, 0u);
+      *reinterpret_cast<uint2*>(dst + 1024 + 8 * lz) = make_uint2(0u, 0u);
+    }
+    planes[t * kDigitTile + 3 * kDigitPlane + lz] = 0;
+  }
+}
+
+// Two 32-row accumulator tiles with samples along the rows of the product
+// (lane: row l % 32 of a tile, samples 8 (v / 4) + 4 (l / 32) + v % 4) to one
+// row per lane: lane l keeps row l of the 64, samples 8 (v / 4) + v % 4 in a
+// and 8 (v / 4) + 4 + v % 4 in b.
+__device__ inline void rows_to_lanes(floatx16& a, floatx16& b) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[v]), __float_as_uint(b[v]), false, false);
+    a[v] = __uint_as_float(r[0]);
+    b[v] = __uint_as_float(r[1]);
+  }
 }
 
 // Row factors: wave w of workgroup g takes activation row 4 g + w, reduces
@@ -119,12 +228,14 @@ __global__ __launch_bounds__(256) void prefill_row_scale_kernel(const void* __re
 // distinct banks.
 constexpr int kXTN = 128, kXTK = 64, kXLd = kXTK + 8;
 
-template <sdq_dtype XT, int kXTM>
+// OUT: 0 writes fp16 x_tilde, 2 or 3 the digit planes of binary or ternary codes
+// (the product is then formed transposed, one row per lane).
+template <sdq_dtype XT, int kXTM, int OUT>
 __global__ __launch_bounds__(256) void expand_prefill_tiled_kernel(
     const void* __restrict__ x, const float* __restrict__ fac, int64_t m, int64_t k, int B, int m_up,
     int64_t k_up, int64_t k_up_pad, const uint16_t* __restrict__ et_hi,
     const uint16_t* __restrict__ et_lo, _Float16* __restrict__ xt_out,
-    _Float16* __restrict__ xt_lo_out) {
+    _Float16* __restrict__ xt_lo_out, DigitPlanes dp) {
   constexpr bool NEED_LO = XT == SDQ_F32;
   __shared__ __attribute__((aligned(16))) _Float16 xs[NEED_LO ? 2 : 1][kXTM * kXLd];
   __shared__ __attribute__((aligned(16))) _Float16 es[2][kXTN * kXLd];
@@ -140,7 +251,7 @@ __global__ __launch_bounds__(256) void expand_prefill_tiled_kernel(
   const int64_t i0 = ((tile / n_st) % n_rt) * kXTM;
   const int64_t b = tile / (n_st * n_rt);
   const int c0 = st * kXTN;                         // first sample of the tile
-  if (b == 0 && st == 0) {
+  if (OUT == 0 && b == 0 && st == 0) {
     const int64_t pad = k_up_pad - k_up;            // zero the padding columns of these rows
     for (int64_t idx = tid; idx < kXTM * pad; idx += 256) {
       const int64_t i = i0 + idx / pad;
@@ -260,11 +371,37 @@ __global__ __launch_bounds__(256) void expand_prefill_tiled_kernel(
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
-          acc[rt][ct] = mfma32(a[rt], bh[ct], acc[rt][ct]);
-          acc[rt][ct] = mfma32(a[rt], bl[ct], acc[rt][ct]);
-          if (NEED_LO) acc[rt][ct] = mfma32(alo[rt], bh[ct], acc[rt][ct]);
+          if constexpr (OUT == 0) {
+            acc[rt][ct] = mfma32(a[rt], bh[ct], acc[rt][ct]);
+            acc[rt][ct] = mfma32(a[rt], bl[ct], acc[rt][ct]);
+            if (NEED_LO) acc[rt][ct] = mfma32(alo[rt], bh[ct], acc[rt][ct]);
+          } else {
+            acc[rt][ct] = mfma32(bh[ct], a[rt], acc[rt][ct]);
+            acc[rt][ct] = mfma32(bl[ct], a[rt], acc[rt][ct]);
+            if (NEED_LO) acc[rt][ct] = mfma32(bh[ct], alo[rt], acc[rt][ct]);
+          }
         }
     }
+  }
+  if constexpr (OUT != 0) {
+    static_assert(RT == 2, "two 32-row tiles per wave");
+    const int64_t row = i0 + 64 * wr + lane;
+    const float pinv = fac[m + min<int64_t>(row, m - 1)];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      const int c = c0 + 64 * wc + 32 * ct;
+      if (c >= m_up) continue;                       // M is a multiple of 32
+      rows_to_lanes(acc[0][ct], acc[1][ct]);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        acc[0][ct][v] *= pinv;
+        acc[1][ct][v] *= pinv;
+      }
+      const int64_t kb = (b * m_up + c) / 32;
+      store_digits<OUT>(acc[0][ct], acc[1][ct], row, dp.n_rg, kb, 32 * (kb + 1) == k_up ? 2 * dp.n_steps : 0,
+                        dp.planes);
+    }
+    return;
   }
 #pragma unroll
   for (int ct = 0; ct < 2; ++ct) {
@@ -316,11 +453,13 @@ constexpr int kEstRsrcWord3 = 0x00020000;   // raw buffer resource, dword 3
 // vmcnt(n) with lgkmcnt(0) (expcnt not waited on).
 constexpr int est_wait_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
-template <sdq_dtype XT, int B>
+// OUT as in the tiled kernel: 2 or 3 writes digit planes, without row factors.
+template <sdq_dtype XT, int B, int OUT>
 __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
     const void* __restrict__ x, const float* __restrict__ fac, int64_t m, int64_t k, int m_up,
     int64_t k_up, int64_t k_up_pad, int64_t nb, int n_ss, int64_t ipg, int64_t n_items,
-    const uint16_t* __restrict__ et_hi, const uint16_t* __restrict__ et_lo, _Float16* __restrict__ xt_out) {
+    const uint16_t* __restrict__ et_hi, const uint16_t* __restrict__ et_lo, _Float16* __restrict__ xt_out,
+    DigitPlanes dp) {
   constexpr int G = B / 8;            // 16-byte groups per x row
   constexpr int KS = B / 16;          // 16-deep k steps
   constexpr int TR = kEstRows;        // x rows per item
@@ -328,8 +467,10 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
   constexpr int TILE = TR * B;        // halves per x tile
   constexpr int RPC = 64 / G;         // rows per 1 KB copy
   constexpr int FC = (TR / 4) / RPC;  // copies per wave per tile (a wave fills TR / 4 rows)
-  constexpr int F = FC + 1;           // copies per wave per item (x and the row factors)
-  constexpr int SPI = (TR / 32) * 4;  // 8-byte stores per lane per item
+  constexpr int F = OUT ? FC : FC + 1;   // copies per wave per item (x, and the row factors of fp16 x_tilde)
+  // Stores per item that a wave is certain to issue (digit planes: none if its
+  // samples lie past M, see below).
+  constexpr int SPI = OUT ? 7 : (TR / 32) * 4;
   static_assert(2 * F + 3 * SPI <= 63, "vmcnt range");
   constexpr bool BF = XT == SDQ_BF16;
   typedef typename std::conditional<BF, bf16x8, half8>::type frag8;
@@ -383,8 +524,10 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
       __builtin_amdgcn_global_load_lds((est_gbl_ptr)src,
                                        (est_lds_ptr)(lds + buf * TILE + ((TR / 4) * wave + RPC * j) * B), 16, 0, 0);
     }
-    const float* src = fac + min<int64_t>(i0 + lane, m - 1);   // every wave its own copy
-    __builtin_amdgcn_global_load_lds((est_gbl_ptr)src, (est_lds_ptr)(pvb + (buf * 4 + wave) * TR), 4, 0, 0);
+    if constexpr (OUT == 0) {
+      const float* src = fac + min<int64_t>(i0 + lane, m - 1);   // every wave its own copy
+      __builtin_amdgcn_global_load_lds((est_gbl_ptr)src, (est_lds_ptr)(pvb + (buf * 4 + wave) * TR), 4, 0, 0);
+    }
   };
   // Ring of NBUF buffers, NBUF - 1 items in flight: item it sits in buffer
   // (it - it_begin) % NBUF.  Per item: wait for its copies (every wave its
@@ -398,7 +541,7 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
   for (int64_t it = it_begin; it < it_end; ++it) {
     const int64_t t = it - it_begin;
     const int cur = static_cast<int>(t % NBUF);
-    if (t == 0) __builtin_amdgcn_s_waitcnt(est_wait_vm_lgkm0(2 * F));
+    if (t == 0 || (OUT && 128 * s + 32 * wave >= m_up)) __builtin_amdgcn_s_waitcnt(est_wait_vm_lgkm0(2 * F));
     else if (t == 1) __builtin_amdgcn_s_waitcnt(est_wait_vm_lgkm0(2 * F + SPI));
     else if (t == 2) __builtin_amdgcn_s_waitcnt(est_wait_vm_lgkm0(2 * F + 2 * SPI));
     else __builtin_amdgcn_s_waitcnt(est_wait_vm_lgkm0(2 * F + 3 * SPI));
@@ -410,6 +553,7 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
     const int64_t i0 = static_cast<int64_t>(rt) * TR;
     const uint16_t* abuf = lds + cur * TILE;
     float pr[TR / 32];
+    if constexpr (OUT == 0)
 #pragma unroll
     for (int r = 0; r < TR / 32; ++r) pr[r] = pvb[(cur * 4 + wave) * TR + 32 * r + lane % 32];
     floatx16 acc[TR / 32];
@@ -432,6 +576,16 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
           acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(el[ks], a, acc[r], 0, 0, 0);
         }
       }
+    }
+    if constexpr (OUT != 0) {
+      const int c = 128 * s + 32 * wave;
+      if (c < m_up) {                                // M is a multiple of 32
+        rows_to_lanes(acc[0], acc[1]);
+        const int64_t kb = (static_cast<int64_t>(b) * m_up + c) / 32;
+        store_digits<OUT>(acc[0], acc[1], i0 + lane, dp.n_rg, kb, 32 * (kb + 1) == k_up ? 2 * dp.n_steps : 0,
+                          dp.planes);
+      }
+      continue;
     }
     // acc[r][v] = x_tilde of row i0 + 32 r + lane % 32, sample
     // 128 s + 32 w + 8 (v / 4) + 4 (lane / 32) + v % 4: four consecutive
@@ -472,29 +626,34 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
 bool prefill_split(const sdq_layout* L) { return L->hadamard == SDQ_HAD_NONE; }
 
 sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                                 const Tables* T, void* ws, hipStream_t stream) {
-  _Float16* xbuf = static_cast<_Float16*>(ws);
+                                 const Tables* T, void* ws, bool digits, hipStream_t stream) {
   const int64_t k_up_pad = L->n_chunks * L->codes_per_chunk;
-  float* fac = reinterpret_cast<float*>(static_cast<char*>(ws) + prefill_planes_bytes(L, m));
-  const dim3 sgrid(static_cast<unsigned>((m + 3) / 4));
-  _Float16* xlo = prefill_split(L)
+  const DigitPlanes dp = digits ? digit_planes(L, m, ws) : DigitPlanes{};
+  _Float16* xbuf = static_cast<_Float16*>(ws);
+  _Float16* xlo = !digits && prefill_split(L)
                       ? reinterpret_cast<_Float16*>(static_cast<char*>(ws) +
                                                     align_up(static_cast<size_t>(m) * k_up_pad * 2, 256))
                       : nullptr;
-  // fp16 / bf16 activations, B = 128 or 256, one fp16 x_tilde: the
-  // E-stationary kernel (SDQ_PREFILL_EXPAND=tiled keeps the tiled one, a
-  // tuning aid).  Workgroups: one per compute unit, spread over the 128-sample
+  float* fac = digits ? dp.row_fac
+                      : reinterpret_cast<float*>(static_cast<char*>(ws) + prefill_planes_bytes(L, m));
+  // fp16 / bf16 activations, B = 128 or 256, no fp16 pair: the E-stationary
+  // kernel.  Workgroups: one per compute unit, spread over the 128-sample
   // slices of M; each walks an even share of the (row tile, block) items.
-  static const char* env = std::getenv("SDQ_PREFILL_EXPAND");
-  const bool tiled_forced = env && std::string(env) == "tiled";
-  const bool estat = !tiled_forced && xt != SDQ_F32 && !xlo && (L->block == 128 || L->block == 256);
-  _Float16* pad_out = estat ? xbuf : nullptr;   // the E-stationary kernel leaves the padding to this one
-  if (xt == SDQ_F32)
-    prefill_row_scale_kernel<SDQ_F32><<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad);
-  else if (xt == SDQ_BF16)
-    prefill_row_scale_kernel<SDQ_BF16><<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad);
-  else
-    prefill_row_scale_kernel<SDQ_F16><<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad);
+  const bool estat = xt != SDQ_F32 && !xlo && (L->block == 128 || L->block == 256);
+  // Row factors: for fp16 x_tilde, and for the fp16 copies of x that the tiled
+  // kernel multiplies.  The E-stationary kernel writes digits without them
+  // (and leaves the padding of fp16 x_tilde to the row factors' kernel).
+  if (!(digits && estat)) {
+    _Float16* pad_out = estat ? xbuf : nullptr;
+    const dim3 sgrid(static_cast<unsigned>((m + 3) / 4));
+    auto scale = [&](auto t) {
+      prefill_row_scale_kernel<decltype(t)::value>
+          <<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad);
+    };
+    if (xt == SDQ_F32) scale(std::integral_constant<sdq_dtype, SDQ_F32>{});
+    else if (xt == SDQ_BF16) scale(std::integral_constant<sdq_dtype, SDQ_BF16>{});
+    else scale(std::integral_constant<sdq_dtype, SDQ_F16>{});
+  }
   if (estat) {
     const int n_ss = (L->m_up + 127) / 128;
     const int64_t n_items = ((m + kEstRows - 1) / kEstRows) * L->nb;
@@ -502,32 +661,45 @@ sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const s
     const int64_t groups = ((cus + n_ss - 1) / n_ss + kXcds - 1) / kXcds * kXcds;
     const int64_t ipg = (n_items + groups - 1) / groups;
     const dim3 egrid(static_cast<unsigned>(n_ss * groups));
-#define SDQ_EST(XT, BB)                                                                          \
-  expand_prefill_estat_kernel<XT, BB><<<egrid, dim3(256), 0, stream>>>(                           \
-      x, fac, m, L->k, L->m_up, L->k_up, k_up_pad, L->nb, n_ss, ipg, n_items, T->et_hi, T->et_lo, xbuf)
-    if (xt == SDQ_BF16) {
-      if (L->block == 256) SDQ_EST(SDQ_BF16, 256);
-      else SDQ_EST(SDQ_BF16, 128);
-    } else {
-      if (L->block == 256) SDQ_EST(SDQ_F16, 256);
-      else SDQ_EST(SDQ_F16, 128);
-    }
+#define SDQ_EST(XT, BB, OUT)                                                                       \
+  expand_prefill_estat_kernel<XT, BB, OUT><<<egrid, dim3(256), 0, stream>>>(                       \
+      x, fac, m, L->k, L->m_up, L->k_up, k_up_pad, L->nb, n_ss, ipg, n_items, T->et_hi, T->et_lo, xbuf, dp)
+#define SDQ_EST_B(XT, OUT)                                                                         \
+  do {                                                                                             \
+    if (L->block == 256) SDQ_EST(XT, 256, OUT);                                                    \
+    else SDQ_EST(XT, 128, OUT);                                                                    \
+  } while (0)
+#define SDQ_EST_X(OUT)                                                                             \
+  do {                                                                                             \
+    if (xt == SDQ_BF16) SDQ_EST_B(SDQ_BF16, OUT);                                                  \
+    else SDQ_EST_B(SDQ_F16, OUT);                                                                  \
+  } while (0)
+    if (!digits) SDQ_EST_X(0);
+    else if (L->levels == 2) SDQ_EST_X(2);
+    else SDQ_EST_X(3);
+#undef SDQ_EST_X
+#undef SDQ_EST_B
 #undef SDQ_EST
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_error(e, "prefill expansion launch");
-    return SDQ_OK;
-  }
-  // Sample tiles fastest: neighbouring workgroups share the x tile.  B is a
-  // multiple of the 64-wide t step for every supported block.
-  constexpr int tm = 128;
-  const dim3 tgrid(static_cast<unsigned>(((L->m_up + kXTN - 1) / kXTN) * L->nb * ((m + tm - 1) / tm)));
-#define SDQ_XT(XT)                                                                              \
-  expand_prefill_tiled_kernel<XT, tm><<<tgrid, dim3(256), 0, stream>>>(                         \
-      x, fac, m, L->k, L->block, L->m_up, L->k_up, k_up_pad, T->et_hi, T->et_lo, xbuf, xlo)
-  if (xt == SDQ_F32) SDQ_XT(SDQ_F32);
-  else if (xt == SDQ_BF16) SDQ_XT(SDQ_BF16);
-  else SDQ_XT(SDQ_F16);
+  } else {
+    // Sample tiles fastest: neighbouring workgroups share the x tile.  B is a
+    // multiple of the 64-wide t step for every supported block.
+    constexpr int tm = 128;
+    const dim3 tgrid(static_cast<unsigned>(((L->m_up + kXTN - 1) / kXTN) * L->nb * ((m + tm - 1) / tm)));
+#define SDQ_XT(XT, OUT)                                                                            \
+  expand_prefill_tiled_kernel<XT, tm, OUT><<<tgrid, dim3(256), 0, stream>>>(                       \
+      x, fac, m, L->k, L->block, L->m_up, L->k_up, k_up_pad, T->et_hi, T->et_lo, xbuf, xlo, dp)
+#define SDQ_XT_X(OUT)                                                                              \
+  do {                                                                                             \
+    if (xt == SDQ_F32) SDQ_XT(SDQ_F32, OUT);                                                       \
+    else if (xt == SDQ_BF16) SDQ_XT(SDQ_BF16, OUT);                                                \
+    else SDQ_XT(SDQ_F16, OUT);                                                                     \
+  } while (0)
+    if (!digits) SDQ_XT_X(0);
+    else if (L->levels == 2) SDQ_XT_X(2);
+    else SDQ_XT_X(3);
+#undef SDQ_XT_X
 #undef SDQ_XT
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "prefill expansion launch");
   return SDQ_OK;

@@ -1,0 +1,461 @@
+// Prefill path of sdq_linear (m > 16 activation rows), the contraction on FP6 x
+// FP4 matrix cores:
+//
+//   gemm     y[i, r] = s_r * sum_j x_tilde[i, j] C[r, j] with x_tilde as three FP6
+//            digit planes (expand_prefill.hip: 15 bits of fixed point and one
+//            power-of-two scale per 32 samples) and the codes as FP4, which
+//            holds +-1, +-2 and 0 exactly: v_mfma_scale_f32_32x32x64_f8f6f4,
+//            one product per plane into the same fp32 sums, the planes'
+//            weights 1, 2^-5, 2^-10 and the block scales as MX scale operands.
+//   reduce   adds the partial sums where K is split over workgroups.
+//
+// Why digits: an FP6 x FP4 product runs at four times the fp16 rate, so three
+// planes take 0.75 of the fp16 matrix time (register-only probes on MI355X,
+// random operands: 6.07 against 1.67 PFLOP/s, 2.0 per three planes), the
+// planes' rounding is below fp16's, and a ternary or binary code becomes its
+// FP4 value in one or two instructions per eight codes (fp16: sixteen).
+//
+// Operand layout of the instruction (checked on the device): lane l supplies
+// row (A) or column (B) l % 32 and the 32 consecutive k of half l / 32, packed
+// low bits first; the scale operand is one byte per lane for its 32 values;
+// accumulator v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A K
+// step is 64 samples.  The digit planes are stored as operand images: per step
+// and 32-row group three planes of 64 lanes x 16 bytes, then 64 lanes x 8
+// bytes, then the 64 block scales, so a tile is copied to LDS as one run and read without conflicts.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "sdq_internal.h"
+
+namespace sdq {
+namespace {
+
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void* dig_lds_ptr;
+typedef __attribute__((address_space(1))) const void* dig_gbl_ptr;
+
+constexpr int kXcdCount = 8;
+constexpr int kDigitBN = 256;        // weight rows per workgroup tile
+
+// vmcnt(n) alone (expcnt and lgkmcnt not waited on).
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0xF70; }
+
+// Workgroup `id` of `total` to a contiguous range per XCD (workgroups are dealt
+// to the eight XCDs round-robin, and each XCD has its own L2).
+__device__ inline int64_t xcd_place(int64_t id, int64_t total) {
+  const int64_t xcd = id % kXcdCount, j = id / kXcdCount;
+  const int64_t per = total / kXcdCount, rem = total % kXcdCount;
+  return xcd * per + (xcd < rem ? xcd : rem) + j;
+}
+
+// The FP4 operand of one column's 32 codes.  Ternary: the 2-bit field f at the
+// top of a nibble is the value 2 code (01 -> 0100 = 2, 11 -> 1100 = -2, 00 -> 0);
+// the odd codes of a word sit there already.  Binary: bit b in the sign of 0010
+// is -code (1 - 2 b); the row scale takes the sign back.
+template <int LEVELS>
+__device__ inline i32x8 fp4_codes(uint32_t w0, uint32_t w1) {
+  i32x8 r = {0, 0, 0, 0, 0, 0, 0, 0};
+  if constexpr (LEVELS == 3) {
+    r[0] = static_cast<int>((w0 << 2) & 0xCCCCCCCCu);
+    r[1] = static_cast<int>(w0 & 0xCCCCCCCCu);
+    r[2] = static_cast<int>((w1 << 2) & 0xCCCCCCCCu);
+    r[3] = static_cast<int>(w1 & 0xCCCCCCCCu);
+  } else {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) r[d] = static_cast<int>(((w0 << (3 - d)) & 0x88888888u) | 0x22222222u);
+  }
+  return r;
+}
+
+struct DigitParts {           // partial sums of a split contraction (splits > 1)
+  float* base = nullptr;
+  int64_t off[kMaxGroup] = {};     // of each linear's [splits][stride]
+  int64_t stride[kMaxGroup] = {};
+};
+
+// WM x WN waves, each RT x CT accumulator tiles of 32 x 32: a workgroup tile of
+// RG = WM RT row groups (32 activation rows each) x 256 weight rows, over the
+// K steps of its split.  x_tilde tiles come straight from global memory to a
+// ring of four LDS buffers three steps ahead, the codes to registers two to
+// three steps ahead; the loop is unrolled over the ring so that the code
+// registers rotate without moves (a move of a load in flight waits for it, and
+// with it for every later copy).  One plain barrier per step with a counted
+// wait: the copies of the next two steps stay in flight.
+template <int LEVELS, int WM, int WN, int RT, int CT, int MINW>
+__global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
+    const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps, int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part) {
+  constexpr int RG = WM * RT;
+  constexpr int W = WM * WN;
+  static_assert(32 * CT * WN == kDigitBN, "tile width");
+  constexpr int TU = RG * kDigitTile / 16;         // 16-byte units of a tile
+  constexpr int NC = (TU + 63) / 64;               // copies of 64 units
+  constexpr int FC = (NC + W - 1) / W;             // copies per wave
+  constexpr int TB = (NC + (NC % W ? 1 : 0)) * 1024;   // LDS bytes per tile (the last KB takes the surplus copies)
+  constexpr int CL = LEVELS == 3 ? CT : 0;         // code loads of every step
+  constexpr int CP = LEVELS == 3 ? 0 : CT;         // code loads of every second step
+  static_assert(2 * (FC + CL) + CP <= 63, "vmcnt range");
+  // Four arrays, not one: in front of an LDS read the compiler waits for every
+  // outstanding copy into the same array.
+  __shared__ __attribute__((aligned(1024))) uint8_t lds0[TB];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds1[TB];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds2[TB];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds3[TB];
+  auto ring = [&](auto jc) -> uint8_t* {
+    constexpr int J = decltype(jc)::value & 3;
+    return J == 0 ? lds0 : J == 1 ? lds1 : J == 2 ? lds2 : lds3;
+  };
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int half = lane / 32;
+  const int wm = wave / WN, wn = wave % WN;
+  // Order of the work: splits slowest, then pairs of row tiles across the column
+  // tiles, so that the workgroups of one XCD share x_tilde and code slices.
+  const int64_t tiles = m_tiles * n_tiles;
+  const int64_t u = xcd_place(blockIdx.x, gridDim.x);
+  const int64_t split = u / tiles, t = u % tiles;
+  const int64_t p = t / (2 * n_tiles), r2 = t % (2 * n_tiles);
+  const int64_t in_pair = min<int64_t>(2, m_tiles - 2 * p);
+  const int64_t nt = r2 / in_pair, mt = 2 * p + r2 % in_pair;
+  int lin = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxGroup; ++i)
+    if (i < S.count && nt >= S.first[i]) lin = i;
+  const int64_t n = S.n[lin];
+  const int64_t n_pad = (n + kPanel - 1) / kPanel * kPanel;
+  const int64_t rg0 = mt * RG;
+  const int64_t n0 = (nt - S.first[lin]) * kDigitBN + wn * 32 * CT;
+  const int it0 = static_cast<int>(split) * steps_per;
+  const int it1 = min(n_steps, it0 + steps_per);
+
+  // Code addresses: this lane's 8 bytes (half `half`) of its columns' chunks,
+  // relative to the tile's first panel.  Columns past the padded rows read the
+  // last row: their outputs are not stored.
+  const uint8_t* __restrict__ cbase =
+      static_cast<const uint8_t*>(S.codes[lin]) + (nt - S.first[lin]) * (kDigitBN / kPanel) * n_chunks * (kPanel * 16);
+  const int col_last = static_cast<int>(n_pad - 1 - (nt - S.first[lin]) * kDigitBN);
+  uint32_t c_off[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const uint32_t col = static_cast<uint32_t>(min(32 * (wn * CT + c) + lane % 32, col_last));
+    c_off[c] = ((col / kPanel) * static_cast<uint32_t>(n_chunks) * kPanel + col % kPanel) * 16 + 8 * half;
+  }
+  // Tile copies: copy j of the tile is 64 lanes x 16 bytes; wave w issues copies
+  // w, w + W, ..., FC of them (one wait count serves all waves, without a branch;
+  // a surplus copy reads one unit and lands past the tile).  Row groups past the
+  // last read the last.
+  uint32_t a_off[FC];
+#pragma unroll
+  for (int j = 0; j < FC; ++j) {
+    const int unit = min(64 * (wave + W * j) + lane, TU - 1);
+    const int rs = static_cast<int>(min<int64_t>(unit / (kDigitTile / 16), n_rg - 1 - rg0));
+    a_off[j] = static_cast<uint32_t>(rs * kDigitTile + 16 * (unit % (kDigitTile / 16)));
+  }
+  auto fill = [&](uint8_t* buf, int it) {
+    const uint8_t* ps = planes + (static_cast<int64_t>(min(it, n_steps - 1)) * n_rg + rg0) * kDigitTile;
+#pragma unroll
+    for (int j = 0; j < FC; ++j)
+      __builtin_amdgcn_global_load_lds((dig_gbl_ptr)(ps + a_off[j]),
+                                       (dig_lds_ptr)(buf + 1024 * min(wave + W * j, NC)), 16, 0, 0);
+  };
+  auto codes = [&](uint2 (&c)[CT], int it) {
+    const int64_t ch = min<int64_t>(LEVELS == 3 ? it : it / 2, n_chunks - 1);
+    const uint8_t* cs = cbase + ch * (kPanel * 16);
+#pragma unroll
+    for (int i = 0; i < CT; ++i) c[i] = *reinterpret_cast<const uint2*>(cs + c_off[i]);
+  };
+  // Wait until at most `n` copies and loads of this wave are outstanding, then
+  // for every wave.  Nothing is scheduled across it.
+  auto landed = [&](auto n) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm(decltype(n)::value));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  floatx16 acc[RT][CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.0f;
+
+  constexpr int CB = LEVELS == 3 ? 4 : 2;          // code register sets: steps, or pairs of steps
+  uint2 cr[CB][CT];
+  // One step: buffer J of the ring, code set of the step; refills the buffer the
+  // previous step read and the code set last used one step (or pair) before.
+  auto step = [&](auto jc, int it) {
+    constexpr int J = decltype(jc)::value;
+    const uint8_t* buf = ring(jc) + wm * RT * kDigitTile;
+    int sa[RT];
+    i32x8 a[3][RT];
+    auto read = [&](int pl) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const uint8_t* ap = buf + r * kDigitTile + pl * kDigitPlane;
+        const uint4 lo = *reinterpret_cast<const uint4*>(ap + 16 * lane);
+        const uint2 hi = *reinterpret_cast<const uint2*>(ap + 1024 + 8 * lane);
+        a[pl][r] = i32x8{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(lo.z),
+                         static_cast<int>(lo.w), static_cast<int>(hi.x), static_cast<int>(hi.y), 0, 0};
+      }
+    };
+    i32x8 b[CT];
+    auto products = [&](int pl) {
+      const int sb = (LEVELS == 3 ? 126 : 127) - 5 * pl;   // plane weight 2^-5pl, codes as 2 code
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+          acc[r][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[pl][r], b[c], acc[r][c], 2, 4, 0, sa[r], 0, sb);
+    };
+    // Every LDS read of the step comes before its refill (the compiler takes a
+    // copy issued in the same step for one into this buffer).
+#pragma unroll
+    for (int r = 0; r < RT; ++r) sa[r] = buf[r * kDigitTile + 3 * kDigitPlane + lane];
+    read(0);
+    read(1);
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const uint2 w = cr[LEVELS == 3 ? J & (CB - 1) : J / 2][c];
+      b[c] = LEVELS == 3 ? fp4_codes<3>(w.x, w.y) : fp4_codes<2>(J % 2 ? w.y : w.x, 0u);
+    }
+    products(0);
+    read(2);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (LEVELS == 3) codes(cr[(J + 3) & (CB - 1)], it + 3);
+    else if constexpr (J % 2 == 0) codes(cr[(J / 2 + 1) & 1], it + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    fill(ring(std::integral_constant<int, J + 3>{}), it + 3);
+    products(1);
+    products(2);
+    // The next step's tile and codes have landed for this lane, and for all after
+    // the barrier: what may be outstanding are the copies and code loads of the
+    // last two steps.  (Binary: a pair's codes come before the copies of the even
+    // step that loads them and must be there after the odd one.  The wait has to
+    // cover the code loads: the compiler would wait for everything in front of
+    // their use if it did not.)
+    landed(std::integral_constant<int, 2 * (FC + CL) + (J % 2 ? 0 : CP)>{});
+  };
+
+  // Each group of loads stays as one (the wait counts here and in the loop count
+  // them).
+  codes(cr[0], it0);
+  fill(lds0, it0);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (LEVELS == 3) codes(cr[1], it0 + 1);
+  fill(lds1, it0 + 1);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (LEVELS == 3) codes(cr[2], it0 + 2);
+  fill(lds2, it0 + 2);
+  landed(std::integral_constant<int, 2 * (FC + CL)>{});
+  for (int it = it0; it < it1; it += 4) {          // n_steps and steps_per are multiples of four
+    step(std::integral_constant<int, 0>{}, it);
+    step(std::integral_constant<int, 1>{}, it + 1);
+    step(std::integral_constant<int, 2>{}, it + 2);
+    step(std::integral_constant<int, 3>{}, it + 3);
+  }
+  // the last copies (never read) land before the workgroup's LDS is released
+  __builtin_amdgcn_s_waitcnt(0);
+
+  const float* __restrict__ scales = S.scales[lin];
+  float* __restrict__ y = part.base ? part.base + part.off[lin] + split * part.stride[lin] : S.y[lin];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int64_t col = n0 + 32 * c + lane % 32;
+    if (col >= n) continue;
+    const float s = LEVELS == 2 ? -scales[col] : scales[col];
+    auto store = [&](auto whole, auto add) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int64_t row = (rg0 + wm * RT + r) * 32 + 8 * (v / 4) + 4 * half + v % 4;
+          if (decltype(whole)::value || row < m) {
+            float* out = y + row * n + col;
+            const float val = acc[r][c][v] * s;
+            *out = decltype(add)::value ? *out + val : val;
+          }
+        }
+    };
+    if (accumulate) store(std::false_type{}, std::true_type{});
+    else if ((rg0 + RG) * 32 <= m) store(std::true_type{}, std::false_type{});
+    else store(std::false_type{}, std::false_type{});
+  }
+}
+
+// y (+)= the sum of a linear's partial sums, in the order of the splits.  V
+// floats per thread and load (4 where y is 16-byte aligned).
+template <int V>
+__global__ __launch_bounds__(256) void reduce_digits_kernel(LinearSet S, DigitParts part, int64_t m, int splits,
+                                                            int accumulate) {
+  const int lin = blockIdx.y;
+  const int64_t cnt = m * S.n[lin];
+  const float* __restrict__ src = part.base + part.off[lin];
+  const int64_t stride = part.stride[lin];
+  float* __restrict__ y = S.y[lin];
+  for (int64_t i = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * V; i < cnt;
+       i += static_cast<int64_t>(gridDim.x) * 256 * V) {
+    if (V == 4 && i + 4 <= cnt) {
+      float4 a = *reinterpret_cast<const float4*>(src + i);
+      for (int s = 1; s < splits; ++s) {
+        const float4 b = *reinterpret_cast<const float4*>(src + s * stride + i);
+        a.x += b.x;
+        a.y += b.y;
+        a.z += b.z;
+        a.w += b.w;
+      }
+      float4* out = reinterpret_cast<float4*>(y + i);
+      if (accumulate) {
+        const float4 b = *out;
+        a.x += b.x;
+        a.y += b.y;
+        a.z += b.z;
+        a.w += b.w;
+      }
+      *out = a;
+    } else {
+      for (int64_t e = i; e < min<int64_t>(cnt, i + V); ++e) {
+        float a = src[e];
+        for (int s = 1; s < splits; ++s) a += src[s * stride + e];
+        y[e] = accumulate ? y[e] + a : a;
+      }
+    }
+  }
+}
+
+// Estimated time of a plan.
+double digit_plan_us(int rg, int sp, int64_t tiles, int64_t quads, int64_t m, int64_t cols, int64_t cus) {
+  const double steps = 4.0 * quads;
+  const double wgs = static_cast<double>((tiles * sp + cus - 1) / cus);     // per CU
+  const double step_us = std::max(rg * 192.0 * 1.35, 350.0) / 2300.0;
+  const double part = sp > 1 ? 2.5 + (sp + 1.0) * m * cols * 8.0 / 6e6 / 1.0 : 0.0;
+  return wgs * (steps * step_us + 2.0) + part;
+}
+
+int64_t column_tiles(const int64_t* n, int count) {
+  int64_t t = 0;
+  for (int j = 0; j < count; ++j) t += (n[j] + kDigitBN - 1) / kDigitBN;
+  return t;
+}
+
+int64_t part_floats(const int64_t* n, int count, int64_t m) {
+  int64_t t = 0;
+  for (int j = 0; j < count; ++j) t += (m * n[j] + 3) / 4 * 4;
+  return t;
+}
+
+}  // namespace
+
+DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws) {
+  DigitPlanes d;
+  d.n_rg = (m + 31) / 32;
+  d.n_steps = 4 * ((L->k_up + 255) / 256);
+  char* base = static_cast<char*>(ws);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* at = base + off;
+    off += align_up(bytes, 256);
+    return at;
+  };
+  d.planes = reinterpret_cast<uint8_t*>(take(static_cast<size_t>(d.n_steps) * d.n_rg * kDigitTile));
+  d.row_fac = reinterpret_cast<float*>(take(static_cast<size_t>(m) * 2 * sizeof(float)));
+  d.bytes = off;
+  return d;
+}
+
+// The split of the contraction.
+DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes) {
+  static const int kRg[] = {1, 2, 3, 4, 6, 8};
+  const int64_t n_rg = (m + 31) / 32, quads = (k_up + 255) / 256, n_tiles = column_tiles(n, count);
+  const int64_t cus = device_compute_units();
+  int64_t cols = 0;
+  for (int j = 0; j < count; ++j) cols += n[j];
+  DigitPlan best;
+  double best_us = 1e30;
+  for (int rg : kRg) {
+    if (rg > n_rg && rg != 1 && (rg / 2 >= n_rg || rg == 3)) continue;
+    const int64_t m_tiles = (n_rg + rg - 1) / rg;
+    const int64_t tiles = m_tiles * n_tiles;
+    for (int sp = 1; sp <= 16; ++sp) {
+      const int64_t per = (quads + sp - 1) / sp;
+      if (sp > 1 && (per < 2 || (sp - 1) * per >= quads)) continue;
+      const size_t need = sp > 1 ? static_cast<size_t>(part_floats(n, count, m)) * sp * sizeof(float) : 0;
+      if (need > part_bytes) break;
+      const double us = digit_plan_us(rg, sp, tiles, per, m, cols, cus);
+      if (us < best_us) {
+        best_us = us;
+        best.rg = rg;
+        best.splits = sp;
+        best.steps_per = static_cast<int>(4 * per);
+        best.part_bytes = need;
+      }
+    }
+  }
+  return best;
+}
+
+sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
+                                 void* part_ws, size_t part_bytes, hipStream_t stream) {
+  S.first[0] = 0;
+  for (int j = 0; j < S.count; ++j) S.first[j + 1] = S.first[j] + (S.n[j] + kDigitBN - 1) / kDigitBN;
+  for (int j = S.count + 1; j <= kMaxGroup; ++j) S.first[j] = S.first[S.count];
+  const DigitPlanes d = digit_planes(L, m, ws);
+  const DigitPlan plan = digit_plan(S.n, S.count, L->k_up, m, part_bytes);
+  const int64_t n_tiles = S.first[S.count];
+  const int64_t m_tiles = (d.n_rg + plan.rg - 1) / plan.rg;
+  DigitParts part;
+  if (plan.splits > 1) {
+    part.base = static_cast<float*>(part_ws);
+    int64_t off = 0;
+    for (int j = 0; j < S.count; ++j) {
+      part.off[j] = off;
+      part.stride[j] = (m * S.n[j] + 3) / 4 * 4;
+      off += part.stride[j] * plan.splits;
+    }
+  }
+  const int acc = accumulate && plan.splits == 1 ? 1 : 0;
+  const dim3 grid(static_cast<unsigned>(m_tiles * n_tiles * plan.splits));
+#define SDQ_DIG(LV, WM, WN, RT, CT, MINW)                                                                \
+  gemm_digits_kernel<LV, WM, WN, RT, CT, MINW><<<grid, dim3(64 * WM * WN), 0, stream>>>(                 \
+      d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,       \
+      plan.steps_per, acc, part)
+#define SDQ_DIG_RG(LV)                                                                                   \
+  switch (plan.rg) {                                                                                     \
+    case 1: SDQ_DIG(LV, 1, 8, 1, 1, 4); break;                                                           \
+    case 2: SDQ_DIG(LV, 2, 4, 1, 2, 4); break;                                                           \
+    case 3: SDQ_DIG(LV, 1, 4, 3, 2, 2); break;                                                           \
+    case 4: SDQ_DIG(LV, 2, 2, 2, 4, 2); break;                                                           \
+    case 6: SDQ_DIG(LV, 2, 4, 3, 2, 2); break;                                                           \
+    default: SDQ_DIG(LV, 4, 2, 2, 4, 2); break;                                                          \
+  }
+  if (L->levels == 2) {
+    SDQ_DIG_RG(2)
+  } else {
+    SDQ_DIG_RG(3)
+  }
+#undef SDQ_DIG_RG
+#undef SDQ_DIG
+  if (plan.splits > 1) {
+    int64_t most = 0;
+    bool al = true;
+    for (int j = 0; j < S.count; ++j) {
+      most = std::max(most, m * S.n[j]);
+      al = al && reinterpret_cast<uintptr_t>(S.y[j]) % 16 == 0;
+    }
+    const int v = al ? 4 : 1;
+    const dim3 rgrid(static_cast<unsigned>(std::min<int64_t>((most + 256 * v - 1) / (256 * v), 4096)),
+                     static_cast<unsigned>(S.count));
+    if (al) reduce_digits_kernel<4><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0);
+    else reduce_digits_kernel<1><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_error(e, "digit-plane GEMM launch");
+  return SDQ_OK;
+}
+
+}  // namespace sdq

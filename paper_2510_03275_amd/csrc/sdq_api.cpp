@@ -461,28 +461,61 @@ static bool needs_unpack(const sdq_layout* L, int64_t m) {
   return L->packing == SDQ_PACK_BASE3 && !(m <= 16 && decode_reads_base3(L, m));
 }
 
-static size_t path_ws_bytes(const sdq_layout* P, int64_t m) {
-  return m <= 16 ? decode_ws_bytes(P, m) : prefill_ws_bytes(P, m);
+static size_t path_ws_bytes(const sdq_layout* P, int64_t m, bool digits = false) {
+  return m <= 16 ? decode_ws_bytes(P, m) : (digits ? digit_planes(P, m, nullptr).bytes : prefill_ws_bytes(P, m));
 }
 
-// Workspace of a linear call over `count` linears of one layout family: the
-// path's part (the expansion at offset 0), then for base-3 codes read as
-// 2-bit fields each linear's unpacked copy.
-static size_t group_ws_bytes(const sdq_layout* Ls, int count, int64_t m) {
-  const sdq_layout* L = &Ls[0];
-  if (!needs_unpack(L, m)) return path_ws_bytes(L, m);
+// The least workspace of a linear call over linears of n[j] rows (layout
+// family L): the path's part (the expansion at offset 0), then for base-3
+// codes read as 2-bit fields each linear's unpacked copy.
+static size_t set_ws_bytes(const sdq_layout* L, const int64_t* n, int count, int64_t m, bool digits = false) {
+  if (!needs_unpack(L, m)) return path_ws_bytes(L, m, digits);
   const sdq_layout F = fields_view(L);
-  size_t off = align_up(path_ws_bytes(&F, m), 256);
-  for (int j = 0; j < count; ++j) off = align_up(off + fields_codes_bytes(&Ls[j]), 256);
+  size_t off = align_up(path_ws_bytes(&F, m, digits), 256);
+  for (int j = 0; j < count; ++j) {
+    sdq_layout Lj = *L;
+    Lj.n = n[j];
+    Lj.n_pad = (n[j] + kPanel - 1) / kPanel * kPanel;
+    off = align_up(off + fields_codes_bytes(&Lj), 256);
+  }
   return off;
+}
+
+static size_t group_ws_bytes(const sdq_layout* Ls, int count, int64_t m) {
+  int64_t n[kMaxGroup] = {};
+  for (int j = 0; j < count; ++j) n[j] = Ls[j].n;
+  return set_ws_bytes(&Ls[0], n, count, m);
 }
 
 static size_t linear_ws_bytes(const sdq_layout* L, int64_t m) { return group_ws_bytes(L, 1, m); }
 
+// The workspace a linear call is best given: for prefill on digit planes their
+// (larger) bytes and the partial sums of a split contraction.  A call accepts
+// any workspace of group_ws_bytes and more and takes what fits.
+static size_t group_ws_wanted(const sdq_layout* Ls, int count, int64_t m) {
+  const size_t least = group_ws_bytes(Ls, count, m);
+  if (m <= 16 || prefill_split(&Ls[0]) || Ls[0].k_up > kDigitMaxK) return least;
+  int64_t n[kMaxGroup] = {};
+  for (int j = 0; j < count; ++j) n[j] = Ls[j].n;
+  const size_t own = align_up(set_ws_bytes(&Ls[0], n, count, m, true), 256);
+  return std::max(least, own + digit_plan(n, count, Ls[0].k_up, m, SIZE_MAX).part_bytes);
+}
+
+// Whether a prefill call runs on digit planes.  In one call (expansion and
+// contraction of the set S) if they and the unpacked codes fit.  An expansion
+// and a contraction called apart (S NULL) decide by what both know: the layout
+// family, m and the workspace size; base-3 layouts, whose unpacked codes depend on
+// the linears, then stay with fp16 x_tilde.
+static bool use_digits(const sdq_layout* L, int64_t m, const LinearSet* S, size_t ws_bytes) {
+  if (m <= 16 || prefill_split(L) || L->k_up > kDigitMaxK) return false;
+  if (S) return set_ws_bytes(L, S->n, S->count, m, true) <= ws_bytes;
+  return L->packing != SDQ_PACK_BASE3 && path_ws_bytes(L, m, true) <= ws_bytes;
+}
+
 size_t sdq_linear_workspace_bytes(const sdq_layout* L, int64_t m) {
   if (check_layout(L) != SDQ_OK || m < 0) return 0;
   if (m == 0) return 0;
-  return linear_ws_bytes(L, m);
+  return group_ws_wanted(L, 1, m);
 }
 
 static sdq_status workspace_ok(size_t need, size_t ws_bytes, const void* ws) {
@@ -507,7 +540,8 @@ static sdq_status linear_common(const sdq_layout* L, int64_t m, size_t ws_bytes,
 // The expansion for layout L; `zero`: the set whose outputs the decode
 // expansion zeroes for a split-K GEMV (or NULL).
 static sdq_status expand_impl(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                              void* ws, const LinearSet* zero, void* stream, bool may_allocate = true) {
+                              void* ws, const LinearSet* zero, bool digits, void* stream,
+                              bool may_allocate = true) {
   if (xt != SDQ_F16 && xt != SDQ_BF16 && xt != SDQ_F32) return set_error(SDQ_ERR_ARG, "bad dtype");
   if (!x) return set_error(SDQ_ERR_ARG, "x is NULL");
   if (!aligned16(x)) return set_error(SDQ_ERR_ARG, "x is not 16-byte aligned");
@@ -518,14 +552,14 @@ static sdq_status expand_impl(const void* x, sdq_dtype xt, int64_t m, const sdq_
   if (st != SDQ_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   return m <= 16 ? launch_decode_expand(x, xt, m, P, T, ws, zero, s)
-                 : launch_prefill_expand(x, xt, m, P, T, ws, s);
+                 : launch_prefill_expand(x, xt, m, P, T, ws, digits, s);
 }
 
 // The contraction of every linear of S (layout family L) against the
 // expansion in ws; base-3 codes on the paths that read 2-bit fields are
 // unpacked first, each into its own part of the workspace.
 static sdq_status contract_impl(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
-                                bool y_ready, void* stream) {
+                                size_t ws_bytes, bool digits, bool y_ready, void* stream) {
   for (int j = 0; j < S.count; ++j) {
     if (!S.codes[j] || !S.scales[j] || !S.y[j]) return set_error(SDQ_ERR_ARG, "NULL pointer argument");
     if (!aligned16(S.codes[j])) return set_error(SDQ_ERR_ARG, "codes are not 16-byte aligned");
@@ -535,7 +569,7 @@ static sdq_status contract_impl(int64_t m, LinearSet S, const sdq_layout* L, boo
   const sdq_layout* P = L;
   if (needs_unpack(L, m)) {
     P = &F;
-    size_t off = align_up(path_ws_bytes(P, m), 256);
+    size_t off = align_up(path_ws_bytes(P, m, digits), 256);
     for (int j = 0; j < S.count; ++j) {
       sdq_layout Lj = *L;
       Lj.n = S.n[j];
@@ -546,6 +580,11 @@ static sdq_status contract_impl(int64_t m, LinearSet S, const sdq_layout* L, boo
       S.codes[j] = fields;
       off = align_up(off + fields_codes_bytes(&Lj), 256);
     }
+  }
+  if (digits) {   // the rest of the workspace holds the partial sums of a split contraction
+    const size_t own = align_up(set_ws_bytes(L, S.n, S.count, m, true), 256);
+    return launch_digit_contract(m, S, P, accumulate, ws, static_cast<char*>(ws) + own,
+                                 ws_bytes > own ? ws_bytes - own : 0, s);
   }
   return m <= 16 ? launch_decode_contract(m, S, P, accumulate, ws, y_ready, s)
                  : launch_prefill_contract(m, S, P, accumulate, ws, s);
@@ -565,7 +604,7 @@ sdq_status sdq_expand_activations(const void* x, sdq_dtype xt, int64_t m, const 
                                   void* ws, size_t ws_bytes, void* stream) {
   sdq_status st = linear_common(L, m, ws_bytes, ws);
   if (st != SDQ_OK || m == 0 || L->n == 0) return st;
-  return expand_impl(x, xt, m, L, ws, nullptr, stream);
+  return expand_impl(x, xt, m, L, ws, nullptr, use_digits(L, m, nullptr, ws_bytes), stream);
 }
 
 sdq_status sdq_linear_expanded(int64_t m, const void* codes, const float* scales,
@@ -573,7 +612,8 @@ sdq_status sdq_linear_expanded(int64_t m, const void* codes, const float* scales
                                size_t ws_bytes, void* stream) {
   sdq_status st = linear_common(L, m, ws_bytes, ws);
   if (st != SDQ_OK || m == 0 || L->n == 0) return st;
-  return contract_impl(m, single_set(codes, scales, L, y), L, accumulate != 0, ws, false, stream);
+  return contract_impl(m, single_set(codes, scales, L, y), L, accumulate != 0, ws, ws_bytes,
+                       use_digits(L, m, nullptr, ws_bytes), false, stream);
 }
 
 // Argument checks of sdq_linear that precede the workspace check.
@@ -593,13 +633,14 @@ static sdq_status linear_args(const void* x, sdq_dtype xt, int64_t m, const void
 // sdq_linear_group).  Decode: the expansion also zeroes y when the GEMV
 // will add into it.
 static sdq_status run_set(const void* x, sdq_dtype xt, int64_t m, const LinearSet& S, const sdq_layout* L,
-                          int32_t accumulate, void* ws, void* stream, bool may_allocate) {
+                          int32_t accumulate, void* ws, size_t ws_bytes, void* stream, bool may_allocate) {
+  const bool digits = use_digits(L, m, &S, ws_bytes);
   const sdq_layout F = fields_view(L);
   const sdq_layout* P = needs_unpack(L, m) ? &F : L;
   const bool zero_in_expand = !accumulate && m <= 16 && decode_needs_zero_y(P, m, set_panels(S));
-  sdq_status st = expand_impl(x, xt, m, L, ws, zero_in_expand ? &S : nullptr, stream, may_allocate);
+  sdq_status st = expand_impl(x, xt, m, L, ws, zero_in_expand ? &S : nullptr, digits, stream, may_allocate);
   if (st != SDQ_OK) return st;
-  return contract_impl(m, S, L, accumulate != 0, ws, true, stream);
+  return contract_impl(m, S, L, accumulate != 0, ws, ws_bytes, digits, true, stream);
 }
 
 }  // extern "C"
@@ -611,7 +652,7 @@ sdq_status sdq::linear_impl(const void* x, sdq_dtype xt, int64_t m, const void* 
   if (st != SDQ_OK || m == 0 || L->n == 0) return st;
   st = linear_common(L, m, ws_bytes, ws);
   if (st != SDQ_OK) return st;
-  return run_set(x, xt, m, single_set(codes, scales, L, y), L, accumulate, ws, stream, may_allocate);
+  return run_set(x, xt, m, single_set(codes, scales, L, y), L, accumulate, ws, ws_bytes, stream, may_allocate);
 }
 
 size_t sdq::linear_ws_need(const sdq_layout* L, int64_t m) {
@@ -648,7 +689,7 @@ static sdq_status check_group(const sdq_layout* Ls, int32_t count) {
 
 size_t sdq_linear_group_workspace_bytes(const sdq_layout* layouts, int32_t count, int64_t m) {
   if (check_group(layouts, count) != SDQ_OK || m <= 0) return 0;
-  return group_ws_bytes(layouts, count, m);
+  return group_ws_wanted(layouts, count, m);
 }
 
 // The set of a group call (empty linears left out) after its checks.
@@ -683,7 +724,7 @@ sdq_status sdq_linear_group(const void* x, sdq_dtype xt, int64_t m, int32_t coun
   sdq_status st = group_set(m, count, codes, scales, layouts, y, ws_bytes, ws, &S);
   if (st != SDQ_OK || m == 0 || S.count == 0) return st;
   if (!x) return set_error(SDQ_ERR_ARG, "x is NULL");
-  return run_set(x, xt, m, S, &layouts[0], accumulate, ws, stream, true);
+  return run_set(x, xt, m, S, &layouts[0], accumulate, ws, ws_bytes, stream, true);
 }
 
 sdq_status sdq_linear_group_expanded(int64_t m, int32_t count, const void* const* codes,
@@ -692,7 +733,8 @@ sdq_status sdq_linear_group_expanded(int64_t m, int32_t count, const void* const
   LinearSet S;
   sdq_status st = group_set(m, count, codes, scales, layouts, y, ws_bytes, ws, &S);
   if (st != SDQ_OK || m == 0 || S.count == 0) return st;
-  return contract_impl(m, S, &layouts[0], accumulate != 0, ws, false, stream);
+  return contract_impl(m, S, &layouts[0], accumulate != 0, ws, ws_bytes,
+                       use_digits(&layouts[0], m, nullptr, ws_bytes), false, stream);
 }
 
 // ---------------------------------------------------------------------------

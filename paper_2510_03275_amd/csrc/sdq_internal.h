@@ -157,10 +157,38 @@ sdq_status launch_decode_contract(int64_t m, LinearSet set, const sdq_layout* L,
 bool prefill_split(const sdq_layout* L);
 size_t prefill_planes_bytes(const sdq_layout* L, int64_t m);
 size_t prefill_ws_bytes(const sdq_layout* L, int64_t m);
+// digits: write x_tilde as digit planes (below) instead of fp16.
 sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                                 const Tables* T, void* ws, hipStream_t stream);
+                                 const Tables* T, void* ws, bool digits, hipStream_t stream);
 sdq_status launch_prefill_contract(int64_t m, LinearSet set, const sdq_layout* L, bool accumulate, void* ws,
                                    hipStream_t stream);
+
+// Prefill on digit planes (layouts with Had): x_tilde as three FP6 planes with a
+// power-of-two scale per 32 samples, as operand images of the FP6 x FP4 matrix
+// cores.  A K step holds 64 samples (their number is rounded up to four, the
+// samples past k_up are zero); rows come in groups of 32.
+//   planes   [n_steps][n_rg][kDigitTile]: per plane 64 lanes x 16 bytes, then
+//            64 lanes x 8 bytes, then 64 block exponents (biased by 127)
+//   row_fac  the row factors p_i and 1 / p_i of the expansions that need them
+constexpr int kDigitPlane = 1536, kDigitTile = 3 * kDigitPlane + 64;
+constexpr int64_t kDigitMaxK = int64_t{1} << 25;   // k_up: a tile's codes are addressed with 32 bits
+struct DigitPlanes {
+  uint8_t* planes = nullptr;
+  float* row_fac = nullptr;
+  int64_t n_rg = 0, n_steps = 0;
+  size_t bytes = 0;
+};
+DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws);
+// How the contraction of `count` linears of n[j] rows is cut: rg row groups
+// (32 activation rows each) per workgroup tile, K in `splits` parts of
+// steps_per steps, with part_bytes of partial sums (at most the bytes given).
+struct DigitPlan {
+  int rg = 1, splits = 1, steps_per = 0;
+  size_t part_bytes = 0;
+};
+DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes);
+sdq_status launch_digit_contract(int64_t m, LinearSet set, const sdq_layout* L, bool accumulate, void* ws,
+                                 void* part_ws, size_t part_bytes, hipStream_t stream);
 
 // Block compensation (Algorithm 1's block loop), fp64.
 sdq_status launch_hessian_accumulate(const float* x, int64_t m, int64_t k, double* h, hipStream_t stream);
