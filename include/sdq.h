@@ -246,7 +246,7 @@ sdq_status sdq_quantize_compensated(const float* w_dev, const sdq_layout* layout
  *                 four 80-code chunks, five 64-code steps), then the fp32
  *                 plane scale of every (row, block);
  *   m > 16:       x_tilde as three FP6 digit planes with a power-of-two scale
- *                 per 32 samples (m rounded up to 32 rows, k_up to 256
+ *                 per 32 samples (m rounded up to 32 rows, k_up to 128
  *                 samples, 73 bytes per 32 samples), the row factors below,
  *                 and the partial sums of a contraction split over K; or,
  *                 for layouts with SDQ_HAD_NONE, an fp16 pair hi + lo of

@@ -33,12 +33,15 @@ namespace sdq {
 namespace {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+// LDS is read through these and not through HIP's uint2 / uint4: reads of class type
+// lose the compiler's knowledge of which buffer they read (see ring_buffer).
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void* dig_lds_ptr;
 typedef __attribute__((address_space(1))) const void* dig_gbl_ptr;
 
 constexpr int kXcdCount = 8;
-constexpr int kDigitBN = 256;        // weight rows per workgroup tile
 
 // vmcnt(n) alone (expcnt and lgkmcnt not waited on).
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0xF70; }
@@ -70,6 +73,14 @@ __device__ inline i32x8 fp4_codes(uint32_t w0, uint32_t w1) {
   return r;
 }
 
+// Buffer J of a workgroup's ring of tiles.  An array each: in front of an LDS read
+// the compiler waits for every outstanding copy into the same array.
+template <int TB, int J>
+__device__ inline uint8_t* ring_buffer() {
+  __shared__ __attribute__((aligned(1024))) uint8_t buf[TB];
+  return buf;
+}
+
 struct DigitParts {           // partial sums of a split contraction (splits > 1)
   float* base = nullptr;
   int64_t off[kMaxGroup] = {};     // of each linear's [splits][stride]
@@ -78,35 +89,31 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 
 // WM x WN waves, each RT x CT accumulator tiles of 32 x 32: a workgroup tile of
 // RG = WM RT row groups (32 activation rows each) x 256 weight rows, over the
-// K steps of its split.  x_tilde tiles come straight from global memory to a
-// ring of four LDS buffers three steps ahead, the codes to registers two to
-// three steps ahead; the loop is unrolled over the ring so that the code
-// registers rotate without moves (a move of a load in flight waits for it, and
-// with it for every later copy).  One plain barrier per step with a counted
-// wait: the copies of the next two steps stay in flight.
-template <int LEVELS, int WM, int WN, int RT, int CT, int MINW>
+// K steps of its split.  The step's x_tilde tile and its codes (four panels, 64
+// rows x 16 bytes each) come straight from global memory to a ring of D LDS
+// buffers, D - 1 steps ahead; one plain barrier per step with a counted wait, so
+// that the copies of the following steps stay in flight.  The codes go through
+// LDS because loads to registers between copies to LDS are served one kind after
+// the other: with the codes loaded to registers in each step, a workgroup paid
+// about one memory latency per step (a 64 x 256 tile, 15 steps: 38 us, against 8
+// without the code loads and 9 without the copies).
+template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
-    const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps, int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part) {
+    const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
+    int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part) {
   constexpr int RG = WM * RT;
   constexpr int W = WM * WN;
-  static_assert(32 * CT * WN == kDigitBN, "tile width");
-  constexpr int TU = RG * kDigitTile / 16;         // 16-byte units of a tile
-  constexpr int NC = (TU + 63) / 64;               // copies of 64 units
+  constexpr int BN = 32 * CT * WN;                 // weight rows of the tile
+  static_assert(BN % kPanel == 0, "whole panels");
+  constexpr int TU = RG * kDigitTile / 16;         // 16-byte units of an x_tilde tile
+  constexpr int NX = (TU + 63) / 64;               // copies of 64 units
+  constexpr int NC = NX + BN / kPanel;       // and one per panel of codes
   constexpr int FC = (NC + W - 1) / W;             // copies per wave
-  constexpr int TB = (NC + (NC % W ? 1 : 0)) * 1024;   // LDS bytes per tile (the last KB takes the surplus copies)
-  constexpr int CL = LEVELS == 3 ? CT : 0;         // code loads of every step
-  constexpr int CP = LEVELS == 3 ? 0 : CT;         // code loads of every second step
-  static_assert(2 * (FC + CL) + CP <= 63, "vmcnt range");
-  // Four arrays, not one: in front of an LDS read the compiler waits for every
-  // outstanding copy into the same array.
-  __shared__ __attribute__((aligned(1024))) uint8_t lds0[TB];
-  __shared__ __attribute__((aligned(1024))) uint8_t lds1[TB];
-  __shared__ __attribute__((aligned(1024))) uint8_t lds2[TB];
-  __shared__ __attribute__((aligned(1024))) uint8_t lds3[TB];
-  auto ring = [&](auto jc) -> uint8_t* {
-    constexpr int J = decltype(jc)::value & 3;
-    return J == 0 ? lds0 : J == 1 ? lds1 : J == 2 ? lds2 : lds3;
-  };
+  constexpr int TB = (NC + (NC % W ? 1 : 0)) * 1024;   // LDS bytes per buffer (the last KB takes the surplus copies)
+  constexpr int CODES = NX * 1024;                 // the codes' place in it
+  static_assert((D - 2) * FC <= 63, "vmcnt range");
+  static_assert(D >= 3 && D <= 5, "ring size");
+  auto ring = [](auto jc) { return ring_buffer<TB, decltype(jc)::value % D>(); };
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int half = lane / 32;
@@ -124,53 +131,45 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
   for (int i = 1; i < kMaxGroup; ++i)
     if (i < S.count && nt >= S.first[i]) lin = i;
   const int64_t n = S.n[lin];
-  const int64_t n_pad = (n + kPanel - 1) / kPanel * kPanel;
   const int64_t rg0 = mt * RG;
-  const int64_t n0 = (nt - S.first[lin]) * kDigitBN + wn * 32 * CT;
+  const int64_t n0 = (nt - S.first[lin]) * BN + wn * 32 * CT;
   const int it0 = static_cast<int>(split) * steps_per;
-  const int it1 = min(n_steps, it0 + steps_per);
+  const int n_it = min(n_steps - it0, steps_per);
 
-  // Code addresses: this lane's 8 bytes (half `half`) of its columns' chunks,
-  // relative to the tile's first panel.  Columns past the padded rows read the
-  // last row: their outputs are not stored.
-  const uint8_t* __restrict__ cbase =
-      static_cast<const uint8_t*>(S.codes[lin]) + (nt - S.first[lin]) * (kDigitBN / kPanel) * n_chunks * (kPanel * 16);
-  const int col_last = static_cast<int>(n_pad - 1 - (nt - S.first[lin]) * kDigitBN);
-  uint32_t c_off[CT];
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    const uint32_t col = static_cast<uint32_t>(min(32 * (wn * CT + c) + lane % 32, col_last));
-    c_off[c] = ((col / kPanel) * static_cast<uint32_t>(n_chunks) * kPanel + col % kPanel) * 16 + 8 * half;
-  }
-  // Tile copies: copy j of the tile is 64 lanes x 16 bytes; wave w issues copies
-  // w, w + W, ..., FC of them (one wait count serves all waves, without a branch;
-  // a surplus copy reads one unit and lands past the tile).  Row groups past the
-  // last read the last.
+  // Copy j of a step is 64 lanes x 16 bytes; wave w issues copies w, w + W, ..., FC
+  // of them (one wait count serves all waves, without a branch; a surplus copy
+  // reads one unit).  Row groups past the last read the last, panels past the
+  // last read the last: what they feed is not stored.
+  const int64_t panels = (n + kPanel - 1) / kPanel, panel0 = (nt - S.first[lin]) * (BN / kPanel);
+  const uint8_t* __restrict__ cbase = static_cast<const uint8_t*>(S.codes[lin]) + panel0 * n_chunks * (kPanel * 16);
   uint32_t a_off[FC];
 #pragma unroll
   for (int j = 0; j < FC; ++j) {
-    const int unit = min(64 * (wave + W * j) + lane, TU - 1);
+    const int cj = wave + W * j;
+    const int unit = min(64 * cj + lane, TU - 1);
     const int rs = static_cast<int>(min<int64_t>(unit / (kDigitTile / 16), n_rg - 1 - rg0));
-    a_off[j] = static_cast<uint32_t>(rs * kDigitTile + 16 * (unit % (kDigitTile / 16)));
+    const int q = static_cast<int>(min<int64_t>(cj - NX, panels - 1 - panel0));
+    a_off[j] = cj >= NC ? 0u
+               : cj < NX ? static_cast<uint32_t>(rs * kDigitTile + 16 * (unit % (kDigitTile / 16)))
+                         : static_cast<uint32_t>(q) * static_cast<uint32_t>(n_chunks) * (kPanel * 16) + 16 * lane;
   }
   auto fill = [&](uint8_t* buf, int it) {
-    const uint8_t* ps = planes + (static_cast<int64_t>(min(it, n_steps - 1)) * n_rg + rg0) * kDigitTile;
-#pragma unroll
-    for (int j = 0; j < FC; ++j)
-      __builtin_amdgcn_global_load_lds((dig_gbl_ptr)(ps + a_off[j]),
-                                       (dig_lds_ptr)(buf + 1024 * min(wave + W * j, NC)), 16, 0, 0);
-  };
-  auto codes = [&](uint2 (&c)[CT], int it) {
-    const int64_t ch = min<int64_t>(LEVELS == 3 ? it : it / 2, n_chunks - 1);
+    const int s = min(it, n_steps - 1);
+    const int64_t ch = min<int64_t>(LEVELS == 3 ? s : s / 2, n_chunks - 1);
+    const uint8_t* ps = planes + (static_cast<int64_t>(s) * n_rg + rg0) * kDigitTile;
     const uint8_t* cs = cbase + ch * (kPanel * 16);
 #pragma unroll
-    for (int i = 0; i < CT; ++i) c[i] = *reinterpret_cast<const uint2*>(cs + c_off[i]);
+    for (int j = 0; j < FC; ++j) {
+      const int cj = wave + W * j;
+      __builtin_amdgcn_global_load_lds((dig_gbl_ptr)((cj < NX ? ps : cs) + a_off[j]),
+                                       (dig_lds_ptr)(buf + 1024 * min(cj, NC)), 16, 0, 0);
+    }
   };
-  // Wait until at most `n` copies and loads of this wave are outstanding, then
-  // for every wave.  Nothing is scheduled across it.
-  auto landed = [&](auto n) {
+  // Wait until at most D - 2 steps' copies of this wave are outstanding, then for
+  // every wave: the next step's are there.  Nothing is scheduled across it.
+  auto landed = [&]() {
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(wait_vm(decltype(n)::value));
+    __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * FC));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -185,21 +184,19 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.0f;
 
-  constexpr int CB = LEVELS == 3 ? 4 : 2;          // code register sets: steps, or pairs of steps
-  uint2 cr[CB][CT];
-  // One step: buffer J of the ring, code set of the step; refills the buffer the
-  // previous step read and the code set last used one step (or pair) before.
+  // One step: reads buffer J, refills the one the previous step read.
   auto step = [&](auto jc, int it) {
     constexpr int J = decltype(jc)::value;
     const uint8_t* buf = ring(jc) + wm * RT * kDigitTile;
+    const uint8_t* cbuf = ring(jc) + CODES + wn * CT * 512 + 16 * (lane % 32) + 8 * half;
     int sa[RT];
     i32x8 a[3][RT];
     auto read = [&](int pl) {
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const uint8_t* ap = buf + r * kDigitTile + pl * kDigitPlane;
-        const uint4 lo = *reinterpret_cast<const uint4*>(ap + 16 * lane);
-        const uint2 hi = *reinterpret_cast<const uint2*>(ap + 1024 + 8 * lane);
+        const u32x4 lo = *reinterpret_cast<const u32x4*>(ap + 16 * lane);
+        const u32x2 hi = *reinterpret_cast<const u32x2*>(ap + 1024 + 8 * lane);
         a[pl][r] = i32x8{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(lo.z),
                          static_cast<int>(lo.w), static_cast<int>(hi.x), static_cast<int>(hi.y), 0, 0};
       }
@@ -216,48 +213,56 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     // Every LDS read of the step comes before its refill (the compiler takes a
     // copy issued in the same step for one into this buffer).
 #pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      if constexpr (LEVELS == 3) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(cbuf + 512 * c);
+        b[c] = fp4_codes<3>(w.x, w.y);
+      } else {   // words 2 half (even steps) and 2 half + 1 (odd steps) of the chunk
+        b[c] = fp4_codes<2>(*reinterpret_cast<const uint32_t*>(cbuf + 512 * c + 4 * (it & 1)), 0u);
+      }
+    }
+#pragma unroll
     for (int r = 0; r < RT; ++r) sa[r] = buf[r * kDigitTile + 3 * kDigitPlane + lane];
     read(0);
     read(1);
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const uint2 w = cr[LEVELS == 3 ? J & (CB - 1) : J / 2][c];
-      b[c] = LEVELS == 3 ? fp4_codes<3>(w.x, w.y) : fp4_codes<2>(J % 2 ? w.y : w.x, 0u);
-    }
     products(0);
     read(2);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (LEVELS == 3) codes(cr[(J + 3) & (CB - 1)], it + 3);
-    else if constexpr (J % 2 == 0) codes(cr[(J / 2 + 1) & 1], it + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    fill(ring(std::integral_constant<int, J + 3>{}), it + 3);
+    fill(ring(std::integral_constant<int, J + D - 1>{}), it + D - 1);
     products(1);
     products(2);
-    // The next step's tile and codes have landed for this lane, and for all after
-    // the barrier: what may be outstanding are the copies and code loads of the
-    // last two steps.  (Binary: a pair's codes come before the copies of the even
-    // step that loads them and must be there after the odd one.  The wait has to
-    // cover the code loads: the compiler would wait for everything in front of
-    // their use if it did not.)
-    landed(std::integral_constant<int, 2 * (FC + CL) + (J % 2 ? 0 : CP)>{});
+    landed();
   };
-
-  // Each group of loads stays as one (the wait counts here and in the loop count
-  // them).
-  codes(cr[0], it0);
-  fill(lds0, it0);
+  using J0 = std::integral_constant<int, 0>;
+  using J1 = std::integral_constant<int, 1>;
+  using J2 = std::integral_constant<int, 2>;
+  using J3 = std::integral_constant<int, 3>;
+  fill(ring(J0{}), it0);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (LEVELS == 3) codes(cr[1], it0 + 1);
-  fill(lds1, it0 + 1);
+  fill(ring(J1{}), it0 + 1);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (LEVELS == 3) codes(cr[2], it0 + 2);
-  fill(lds2, it0 + 2);
-  landed(std::integral_constant<int, 2 * (FC + CL)>{});
-  for (int it = it0; it < it1; it += 4) {          // n_steps and steps_per are multiples of four
-    step(std::integral_constant<int, 0>{}, it);
-    step(std::integral_constant<int, 1>{}, it + 1);
-    step(std::integral_constant<int, 2>{}, it + 2);
-    step(std::integral_constant<int, 3>{}, it + 3);
+  if constexpr (D >= 4) fill(ring(J2{}), it0 + 2);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (D >= 5) fill(ring(J3{}), it0 + 3);
+  landed();
+  int it = it0;
+  for (const int whole = it0 + n_it / D * D; it < whole; it += D) {
+    step(J0{}, it);
+    step(J1{}, it + 1);
+    step(J2{}, it + 2);
+    if constexpr (D >= 4) step(J3{}, it + 3);
+    if constexpr (D >= 5) step(std::integral_constant<int, 4>{}, it + 4);
+  }
+  const int rest = it0 + n_it - it;
+  if (rest > 0) {
+    step(J0{}, it);
+    if (rest > 1) {
+      step(J1{}, it + 1);
+      if (D >= 4 && rest > 2) {
+        step(J2{}, it + 2);
+        if (D >= 5 && rest > 3) step(J3{}, it + 3);
+      }
+    }
   }
   // the last copies (never read) land before the workgroup's LDS is released
   __builtin_amdgcn_s_waitcnt(0);
@@ -328,18 +333,38 @@ __global__ __launch_bounds__(256) void reduce_digits_kernel(LinearSet S, DigitPa
   }
 }
 
-// Estimated time of a plan.
-double digit_plan_us(int rg, int sp, int64_t tiles, int64_t quads, int64_t m, int64_t cols, int64_t cus) {
-  const double steps = 4.0 * quads;
-  const double wgs = static_cast<double>((tiles * sp + cus - 1) / cus);     // per CU
-  const double step_us = std::max(rg * 192.0 * 1.35, 350.0) / 2300.0;
-  const double part = sp > 1 ? 2.5 + (sp + 1.0) * m * cols * 8.0 / 6e6 / 1.0 : 0.0;
-  return wgs * (steps * step_us + 2.0) + part;
+// The tile shapes: row groups x weight rows, the workgroups that fit a CU, and
+// the time (us) of a K step on a CU that runs one of them, and of each where
+// several run.  Fitted, as are the costs of the partial sums below, to 3700
+// timings of contractions on MI355X (12 groups of linears with k_up 960 to 24576
+// and 700 to 28672 rows, m 17 to 2048, 1 to 16 splits): within 6 % for half of
+// them; the plan chosen is 2.2 % slower than the best of the three shapes and all
+// splits on average, 14 % at most.  Of nine shapes timed these three are within
+// 0.5 % of the best of all on average: 32 x 256 (many short tiles) up to a few
+// hundred rows, 128 x 512 for large products (28672 x 16384 at m = 2048: 1196 us,
+// 64 x 512 1204, 128 x 256 1266, 256 x 256 1308, 32 x 256 1438), where wide
+// tiles matter because x_tilde takes nine times the bytes of the codes.
+struct DigitShape {
+  int rg, bn, per_cu;
+  double step_us, step_each_us;
+};
+constexpr DigitShape kShapes[] = {
+    {1, 256, 4, 0.273, 0.170},  // 4 waves, each 32 x 64
+    {2, 512, 2, 0.680, 0.534},  // 4 waves, each 64 x 128
+    {4, 512, 1, 1.137, 1.137},  // 2 x 4 waves, each 64 x 128
+};
+
+// Estimated time of a plan (up to a constant).
+double digit_plan_us(const DigitShape& s, int sp, int64_t tiles, int64_t steps, double outs, int64_t cus) {
+  const int64_t on_cu = (tiles * sp + cus - 1) / cus;
+  const int64_t full = on_cu / s.per_cu, rest = on_cu % s.per_cu;
+  const double step = full * s.per_cu * s.step_each_us + (rest ? std::max(s.step_us, rest * s.step_each_us) : 0.0);
+  return step * steps + (sp > 1 ? 2.1 + (sp + 1) * outs * 1.18e-6 : 0.0);
 }
 
-int64_t column_tiles(const int64_t* n, int count) {
+int64_t column_tiles(const int64_t* n, int count, int bn) {
   int64_t t = 0;
-  for (int j = 0; j < count; ++j) t += (n[j] + kDigitBN - 1) / kDigitBN;
+  for (int j = 0; j < count; ++j) t += (n[j] + bn - 1) / bn;
   return t;
 }
 
@@ -354,7 +379,7 @@ int64_t part_floats(const int64_t* n, int count, int64_t m) {
 DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws) {
   DigitPlanes d;
   d.n_rg = (m + 31) / 32;
-  d.n_steps = 4 * ((L->k_up + 255) / 256);
+  d.n_steps = 2 * ((L->k_up + 127) / 128);
   char* base = static_cast<char*>(ws);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -370,29 +395,26 @@ DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws) {
 
 // The split of the contraction.
 DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes) {
-  static const int kRg[] = {1, 2, 3, 4, 6, 8};
-  const int64_t n_rg = (m + 31) / 32, quads = (k_up + 255) / 256, n_tiles = column_tiles(n, count);
+  const int64_t n_rg = (m + 31) / 32, pairs = (k_up + 127) / 128;
   const int64_t cus = device_compute_units();
-  int64_t cols = 0;
-  for (int j = 0; j < count; ++j) cols += n[j];
+  double outs = 0;
+  for (int j = 0; j < count; ++j) outs += static_cast<double>(m) * n[j];
+  const size_t one_part = static_cast<size_t>(part_floats(n, count, m)) * sizeof(float);
   DigitPlan best;
   double best_us = 1e30;
-  for (int rg : kRg) {
-    if (rg > n_rg && rg != 1 && (rg / 2 >= n_rg || rg == 3)) continue;
-    const int64_t m_tiles = (n_rg + rg - 1) / rg;
-    const int64_t tiles = m_tiles * n_tiles;
+  for (int i = 0; i < static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
+    const int64_t tiles = (n_rg + kShapes[i].rg - 1) / kShapes[i].rg * column_tiles(n, count, kShapes[i].bn);
     for (int sp = 1; sp <= 16; ++sp) {
-      const int64_t per = (quads + sp - 1) / sp;
-      if (sp > 1 && (per < 2 || (sp - 1) * per >= quads)) continue;
-      const size_t need = sp > 1 ? static_cast<size_t>(part_floats(n, count, m)) * sp * sizeof(float) : 0;
-      if (need > part_bytes) break;
-      const double us = digit_plan_us(rg, sp, tiles, per, m, cols, cus);
+      const int64_t per = (pairs + sp - 1) / sp;
+      if (sp > 1 && ((sp - 1) * per >= pairs || tiles * (sp - 1) >= 4 * cus)) continue;
+      if (sp > 1 && one_part * sp > part_bytes) break;
+      const double us = digit_plan_us(kShapes[i], sp, tiles, 2 * per, outs, cus);
       if (us < best_us) {
         best_us = us;
-        best.rg = rg;
+        best.shape = i;
         best.splits = sp;
-        best.steps_per = static_cast<int>(4 * per);
-        best.part_bytes = need;
+        best.steps_per = static_cast<int>(2 * per);
+        best.part_bytes = sp > 1 ? one_part * sp : 0;
       }
     }
   }
@@ -401,13 +423,14 @@ DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_
 
 sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
                                  void* part_ws, size_t part_bytes, hipStream_t stream) {
-  S.first[0] = 0;
-  for (int j = 0; j < S.count; ++j) S.first[j + 1] = S.first[j] + (S.n[j] + kDigitBN - 1) / kDigitBN;
-  for (int j = S.count + 1; j <= kMaxGroup; ++j) S.first[j] = S.first[S.count];
   const DigitPlanes d = digit_planes(L, m, ws);
   const DigitPlan plan = digit_plan(S.n, S.count, L->k_up, m, part_bytes);
+  const DigitShape& shape = kShapes[plan.shape];
+  S.first[0] = 0;
+  for (int j = 0; j < S.count; ++j) S.first[j + 1] = S.first[j] + (S.n[j] + shape.bn - 1) / shape.bn;
+  for (int j = S.count + 1; j <= kMaxGroup; ++j) S.first[j] = S.first[S.count];
   const int64_t n_tiles = S.first[S.count];
-  const int64_t m_tiles = (d.n_rg + plan.rg - 1) / plan.rg;
+  const int64_t m_tiles = (d.n_rg + shape.rg - 1) / shape.rg;
   DigitParts part;
   if (plan.splits > 1) {
     part.base = static_cast<float*>(part_ws);
@@ -420,25 +443,25 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
   }
   const int acc = accumulate && plan.splits == 1 ? 1 : 0;
   const dim3 grid(static_cast<unsigned>(m_tiles * n_tiles * plan.splits));
-#define SDQ_DIG(LV, WM, WN, RT, CT, MINW)                                                                \
-  gemm_digits_kernel<LV, WM, WN, RT, CT, MINW><<<grid, dim3(64 * WM * WN), 0, stream>>>(                 \
-      d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,       \
-      plan.steps_per, acc, part)
-#define SDQ_DIG_RG(LV)                                                                                   \
-  switch (plan.rg) {                                                                                     \
-    case 1: SDQ_DIG(LV, 1, 8, 1, 1, 4); break;                                                           \
-    case 2: SDQ_DIG(LV, 2, 4, 1, 2, 4); break;                                                           \
-    case 3: SDQ_DIG(LV, 1, 4, 3, 2, 2); break;                                                           \
-    case 4: SDQ_DIG(LV, 2, 2, 2, 4, 2); break;                                                           \
-    case 6: SDQ_DIG(LV, 2, 4, 3, 2, 2); break;                                                           \
-    default: SDQ_DIG(LV, 4, 2, 2, 4, 2); break;                                                          \
+#define SDQ_DIG(LV, I, WM, WN, RT, CT, MINW, D)                                                           \
+  case I:                                                                                                \
+    static_assert(kShapes[I].rg == WM * RT && kShapes[I].bn == 32 * WN * CT, "shape");                   \
+    gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, D><<<grid, dim3(64 * WM * WN), 0, stream>>>(            \
+        d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,              \
+        plan.steps_per, acc, part);                                                                      \
+    break
+#define SDQ_DIG_SHAPES(LV)                                                                               \
+  switch (plan.shape) {                                                                                  \
+    SDQ_DIG(LV, 0, 1, 4, 1, 2, 4, 4);                                                                    \
+    SDQ_DIG(LV, 1, 1, 4, 2, 4, 2, 4);                                                                    \
+    SDQ_DIG(LV, 2, 2, 4, 2, 4, 2, 5);                                                                    \
   }
   if (L->levels == 2) {
-    SDQ_DIG_RG(2)
+    SDQ_DIG_SHAPES(2)
   } else {
-    SDQ_DIG_RG(3)
+    SDQ_DIG_SHAPES(3)
   }
-#undef SDQ_DIG_RG
+#undef SDQ_DIG_SHAPES
 #undef SDQ_DIG
   if (plan.splits > 1) {
     int64_t most = 0;

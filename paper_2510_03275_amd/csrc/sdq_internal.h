@@ -165,7 +165,7 @@ sdq_status launch_prefill_contract(int64_t m, LinearSet set, const sdq_layout* L
 
 // Prefill on digit planes (layouts with Had): x_tilde as three FP6 planes with a
 // power-of-two scale per 32 samples, as operand images of the FP6 x FP4 matrix
-// cores.  A K step holds 64 samples (their number is rounded up to four, the
+// cores.  A K step holds 64 samples (their number is rounded up to two, the
 // samples past k_up are zero); rows come in groups of 32.
 //   planes   [n_steps][n_rg][kDigitTile]: per plane 64 lanes x 16 bytes, then
 //            64 lanes x 8 bytes, then 64 block exponents (biased by 127)
@@ -179,11 +179,11 @@ struct DigitPlanes {
   size_t bytes = 0;
 };
 DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws);
-// How the contraction of `count` linears of n[j] rows is cut: rg row groups
-// (32 activation rows each) per workgroup tile, K in `splits` parts of
-// steps_per steps, with part_bytes of partial sums (at most the bytes given).
+// How the contraction of `count` linears of n[j] rows is cut: the tile shape (an
+// index of the contraction's own), K in `splits` parts of steps_per steps, with
+// part_bytes of partial sums (at most the bytes given).
 struct DigitPlan {
-  int rg = 1, splits = 1, steps_per = 0;
+  int shape = 0, splits = 1, steps_per = 0;
   size_t part_bytes = 0;
 };
 DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes);

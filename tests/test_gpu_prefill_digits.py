@@ -44,7 +44,7 @@ def _check(y, x64, r, block=256, bound=BOUND):
     assert _rel(y, y_ref) <= bound, _rel(y, y_ref)
 
 
-# every row-group count of the tiles (1, 2, 3, 4, 6, 8 groups of 32) with full and partial groups
+# tiles of 1, 2 and 4 groups of 32 rows, full and partial
 @pytest.mark.parametrize("m", [17, 32, 33, 64, 65, 96, 97, 128, 161, 192, 193, 256, 257])
 @pytest.mark.parametrize("n,k,osr,levels", [(300, 1280, 2.0, 3), (257, 1280, 1.625, 2), (64, 512, 2.125, 3)])
 def test_tile_edges(n, k, osr, levels, m):
@@ -127,3 +127,21 @@ def test_nonfinite_activations_stay_in_their_rows():
         assert not torch.isfinite(y[rows]).any()
         assert torch.isfinite(y[~rows]).all()
     assert torch.equal(P.linear(bad, enc)[~rows], want[~rows])
+
+
+# sizes at which each tile shape is chosen (32 x 256, 64 x 512, 128 x 512), split and unsplit, the
+# last column tile and row tile partial, and a group of linears
+@pytest.mark.parametrize("ns,k,m,levels", [([9000], 256, 60, 3), ([6100], 512, 700, 2), ([12300], 512, 1500, 3),
+                                           ([1300, 4000, 70], 768, 300, 3), ([2100], 4096, 900, 2)])
+def test_tile_shapes_and_groups(ns, k, m, levels):
+    torch = require_gpu()
+    import paper_2510_03275_amd as P
+    made = [_encoded(torch, n, k, 1.5, levels, seed=n) for n in ns]
+    ys = [torch.full((m, n), float("nan"), device="cuda") for n in ns]
+    group = P.LinearGroup([e for e, _ in made], ys)
+    ws = torch.empty(P.sdq_linear_group_workspace_bytes([e.layout for e, _ in made], m), dtype=torch.uint8,
+                     device="cuda")
+    x, x64 = to_device_x(synth.activations_f32(m, 6, m, k), "bf16", torch)
+    P.sdq_linear_group(x, group, ws)
+    for y, (_, r) in zip(ys, made):
+        _check(y, x64, r)
