@@ -37,6 +37,7 @@ constexpr int kUpBM = 128;        // rows per upsample tile (two panels)
 constexpr int kUpBN = 64;         // non-impulse samples per upsample tile
 constexpr int kUpBK = 16;         // t-chunk staged in LDS (two buffers)
 constexpr int kUpThreads = 128;   // 16 x 8 threads, 8 x 8 outputs each
+constexpr int64_t kUpSmall = 1024;   // tiles of 128 x 64 from which a launch uses them
 constexpr int kScanWaves = 4;
 
 __global__ void clear_kernel(uint32_t* __restrict__ flag, uint32_t* __restrict__ rmax, int64_t n) {
@@ -58,9 +59,11 @@ struct SignMask {
 // h = 1, 2 (bits of e), 4, 8 (bits of q: partner lanes xor 1, 2), 16, ...,
 // B/2 (bits of j); every stage pairs the same elements and rounds the same
 // sums and differences as the textbook loop, so the result is bit-identical.
-template <int B>
+// W: float, or double (rounded to fp32 as it is read: the compensated encoder's
+// corrected weights).
+template <int B, typename W>
 __global__ __launch_bounds__(kRotThreads) void rotate_kernel(
-    const float* __restrict__ w, int64_t n, int64_t k, int64_t n_ws, int64_t k_up, int m_up,
+    const W* __restrict__ w, int64_t n, int64_t k, int64_t n_ws, int64_t k_up, int m_up,
     int g0, int phases, int had, SignMask sm, float inv_sqrt_b, float* __restrict__ v,
     float* __restrict__ xup, uint32_t* __restrict__ rmax, uint32_t* __restrict__ flag) {
   constexpr int J = B / 16;
@@ -73,11 +76,21 @@ __global__ __launch_bounds__(kRotThreads) void rotate_kernel(
   float x[J][4];
   bool bad = false;
   if (r < n) {
-    const float4* src = reinterpret_cast<const float4*>(w + r * k + b * B) + q;
+    if constexpr (sizeof(W) == 4) {
+      const float4* src = reinterpret_cast<const float4*>(w + r * k + b * B) + q;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const float4 t4 = src[4 * j];
-      x[j][0] = t4.x; x[j][1] = t4.y; x[j][2] = t4.z; x[j][3] = t4.w;
+      for (int j = 0; j < J; ++j) {
+        const float4 t4 = src[4 * j];
+        x[j][0] = t4.x; x[j][1] = t4.y; x[j][2] = t4.z; x[j][3] = t4.w;
+      }
+    } else {
+      const double2* src = reinterpret_cast<const double2*>(w + r * k + b * B) + 2 * q;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const double2 lo = src[8 * j], hi = src[8 * j + 1];
+        x[j][0] = static_cast<float>(lo.x); x[j][1] = static_cast<float>(lo.y);
+        x[j][2] = static_cast<float>(hi.x); x[j][3] = static_cast<float>(hi.y);
+      }
     }
 #pragma unroll
     for (int j = 0; j < J; ++j)
@@ -183,21 +196,31 @@ __device__ inline void lds_barrier() {
 }
 
 // Batched VALU GEMM over (block, row tile, sample tile).  Thread (tx, ty)
-// owns rows ty*8 .. ty*8+7 and tile columns tx*8 .. tx*8+7.  The t chunks
+// owns rows ty*T .. ty*T+T-1 and tile columns tx*T .. tx*T+T-1 of a tile of 16 T
+// rows x 8 T samples: T = 8 (two LDS bytes per multiply-add), or T = 4 where a
+// launch has few tiles: one block of 4096 rows is 128 workgroups of the large
+// tile and 76 us at OSR 2, 512 of the small one and 25 us.
+// The large launches run at 73 % of the vector unit's issue rate (a rounded
+// product and a rounded sum per term; packed and fused forms would round
+// differently or are not used).  The t chunks
 // are copied from global memory straight into two LDS buffers
 // (global_load_lds_dwordx4: 1 KB per wave and copy, no staging registers);
 // chunk c + 2 is copied while chunk c + 1 is multiplied.  Every output adds
 // its products in increasing t, as a plain loop over t would.
+template <int T>
 __global__ __launch_bounds__(kUpThreads) void upsample_kernel(
     const float* __restrict__ v, const float* __restrict__ unz, int64_t n, int64_t n_ws,
     int64_t k_up, int B, int m_up, int phases, int m_nz, int m_nz_pad, float* __restrict__ xup,
     uint32_t* __restrict__ rmax) {
-  static_assert(kUpThreads == 128 && kUpBK == 16 && kUpBM == 128 && kUpBN == 64,
-                "copy pattern: each wave copies 8 of the 16 t rows of both operands");
-  __shared__ __attribute__((aligned(1024))) float As0[kUpBK][kUpBM];
-  __shared__ __attribute__((aligned(1024))) float As1[kUpBK][kUpBM];
-  __shared__ __attribute__((aligned(1024))) float Bs0[kUpBK][kUpBN];
-  __shared__ __attribute__((aligned(1024))) float Bs1[kUpBK][kUpBN];
+  static_assert(kUpThreads == 128 && kUpBK == 16 && kUpBM == 128 && kUpBN == 64 && (T == 4 || T == 8),
+                "copy pattern: each wave copies half of the t rows of both operands");
+  constexpr int BM = 16 * T, BN = 8 * T;            // the tile (at most kUpBM x kUpBN)
+  constexpr int AR = 256 / BM, BR = 256 / BN;       // t rows per 1 KB copy
+  constexpr int BK = T == 8 ? kUpBK : 2 * kUpBK;    // t chunk: the small tile multiplies less per copy latency
+  __shared__ __attribute__((aligned(1024))) float As0[BK][BM];
+  __shared__ __attribute__((aligned(1024))) float As1[BK][BM];
+  __shared__ __attribute__((aligned(1024))) float Bs0[BK][BN];
+  __shared__ __attribute__((aligned(1024))) float Bs1[BK][BN];
   const int tid = threadIdx.x;
   const int lane = tid % 64;
   const int wave = tid / 64;
@@ -206,54 +229,54 @@ __global__ __launch_bounds__(kUpThreads) void upsample_kernel(
   const int64_t rt = blockIdx.x;     // row tile
   const int jt = blockIdx.y;         // sample tile
   const int64_t b = blockIdx.z;      // block
-  const int64_t r0 = rt * kUpBM;
-  const int j0 = jt * kUpBN;
-  float acc[8][8];
+  const int64_t r0 = rt * BM;
+  const int j0 = jt * BN;
+  float acc[T][T];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
+    for (int j = 0; j < T; ++j) acc[i][j] = 0.0f;
 
-  // Copies of one chunk by wave w: t rows 8w .. 8w+7 of A (four copies of
-  // two 512-byte rows) and of B (two copies of four 256-byte rows).  Lane l
-  // of a copy lands 16 l bytes past the copy's LDS base, so the global
+  // Copies of one chunk by wave w: half of the t rows of A (AR rows a copy)
+  // and of B (BR rows a copy).  Lane l of a copy lands 16 l bytes past the copy's LDS base, so the global
   // source of lane l is the float4 that belongs there.
-  const float* a_src = v + b * B * n_ws + (8 * wave + lane / 32) * n_ws + r0 + (lane % 32) * 4;
-  const float* b_src = unz + (8 * wave + lane / 16) * m_nz_pad + j0 + (lane % 16) * 4;
+  const float* a_src = v + b * B * n_ws + ((BK / 2) * wave + lane / (BM / 4)) * n_ws + r0 + (lane % (BM / 4)) * 4;
+  const float* b_src = unz + ((BK / 2) * wave + lane / (BN / 4)) * m_nz_pad + j0 + (lane % (BN / 4)) * 4;
 #define SDQ_UP_FILL(AS, BS, C)                                                                    \
   do {                                                                                            \
-    const int64_t t0_ = static_cast<int64_t>(C) * kUpBK;                                          \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                 \
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)(a_src + (t0_ + 2 * j) * n_ws),              \
-                                       (lds_void_ptr)(&AS[8 * wave + 2 * j][0]), 16, 0, 0);       \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                 \
-      __builtin_amdgcn_global_load_lds((gbl_void_ptr)(b_src + (t0_ + 4 * j) * m_nz_pad),          \
-                                       (lds_void_ptr)(&BS[8 * wave + 4 * j][0]), 16, 0, 0);       \
+    const int64_t t0_ = static_cast<int64_t>(C) * BK;                                          \
+    _Pragma("unroll") for (int j = 0; j < BK / 2; j += AR)                                             \
+      __builtin_amdgcn_global_load_lds((gbl_void_ptr)(a_src + (t0_ + j) * n_ws),                  \
+                                       (lds_void_ptr)(&AS[(BK / 2) * wave + j][0]), 16, 0, 0);           \
+    _Pragma("unroll") for (int j = 0; j < BK / 2; j += BR)                                             \
+      __builtin_amdgcn_global_load_lds((gbl_void_ptr)(b_src + (t0_ + j) * m_nz_pad),              \
+                                       (lds_void_ptr)(&BS[(BK / 2) * wave + j][0]), 16, 0, 0);           \
   } while (0)
 #define SDQ_UP_MUL(AS, BS)                                                                        \
   do {                                                                                            \
-    _Pragma("unroll 4") for (int tt = 0; tt < kUpBK; ++tt) {                                      \
-      const float4 a0 = *reinterpret_cast<const float4*>(&AS[tt][ty * 8]);                        \
-      const float4 a1 = *reinterpret_cast<const float4*>(&AS[tt][ty * 8 + 4]);                    \
-      const float4 b0 = *reinterpret_cast<const float4*>(&BS[tt][tx * 8]);                        \
-      const float4 b1 = *reinterpret_cast<const float4*>(&BS[tt][tx * 8 + 4]);                    \
-      const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};                        \
-      const float c[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};                        \
-      _Pragma("unroll") for (int i = 0; i < 8; ++i)                                               \
-        _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                           \
+    _Pragma("unroll 4") for (int tt = 0; tt < BK; ++tt) {                                      \
+      float a[T], c[T];                                                                           \
+      _Pragma("unroll") for (int i = 0; i < T; i += 4) {                                          \
+        const float4 av = *reinterpret_cast<const float4*>(&AS[tt][ty * T + i]);                  \
+        const float4 bv = *reinterpret_cast<const float4*>(&BS[tt][tx * T + i]);                  \
+        a[i] = av.x; a[i + 1] = av.y; a[i + 2] = av.z; a[i + 3] = av.w;                           \
+        c[i] = bv.x; c[i + 1] = bv.y; c[i + 2] = bv.z; c[i + 3] = bv.w;                           \
+      }                                                                                           \
+      _Pragma("unroll") for (int i = 0; i < T; ++i)                                               \
+        _Pragma("unroll") for (int j = 0; j < T; ++j) {                                           \
           const float prod = a[i] * c[j];                                                         \
           acc[i][j] = acc[i][j] + prod;                                                           \
         }                                                                                         \
     }                                                                                             \
   } while (0)
 
-  // nc = B / 16 is even (B is 64, 128 or 256).  Chunk c + 1 is copied while
+  // nc = B / BK is even (B is 64, 128 or 256).  Chunk c + 1 is copied while
   // chunk c is multiplied; then a wait for this wave's copies (vmcnt 0) and
   // a barrier make every wave's copies visible and order the refill of a
   // buffer after every read of it.  No copy is in flight where the loop
   // closes, so the compiler can tell each buffer's reads from the other
   // buffer's copies and adds no wait of its own before them.
-  const int nc = B / kUpBK;
+  const int nc = B / BK;
   SDQ_UP_FILL(As0, Bs0, 0);
   __builtin_amdgcn_s_waitcnt(0xF70);
   lds_barrier();
@@ -270,27 +293,28 @@ __global__ __launch_bounds__(kUpThreads) void upsample_kernel(
 #undef SDQ_UP_FILL
 #undef SDQ_UP_MUL
   // Store: sample j -> m = (j / (P-1)) * P + j % (P-1) + 1; rows are contiguous.
-  float mx[8];
+  float mx[T];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) mx[i] = 0.0f;
-  const int64_t rbase = r0 + ty * 8;          // 8 rows inside one panel
+  for (int i = 0; i < T; ++i) mx[i] = 0.0f;
+  const int64_t rbase = r0 + ty * T;          // T rows inside one panel
   const int64_t panel = rbase / kPanel;
   const int lane_row = static_cast<int>(rbase % kPanel);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int jj = j0 + tx * 8 + j;
+  for (int j = 0; j < T; ++j) {
+    const int jj = j0 + tx * T + j;
     if (jj < m_nz) {
       const int m = (jj / (phases - 1)) * phases + jj % (phases - 1) + 1;
       float* dst = xup + (panel * k_up + b * m_up + m) * kPanel + lane_row;
-      *reinterpret_cast<float4*>(dst) = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4][j], acc[5][j], acc[6][j], acc[7][j]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) mx[i] = fmaxf(mx[i], fabsf(acc[i][j]));
+      for (int i = 0; i < T; i += 4)
+        *reinterpret_cast<float4*>(dst + i) = make_float4(acc[i][j], acc[i + 1][j], acc[i + 2][j], acc[i + 3][j]);
+#pragma unroll
+      for (int i = 0; i < T; ++i) mx[i] = fmaxf(mx[i], fabsf(acc[i][j]));
     }
   }
   // Reduce the maxima over the 8 threads (tx) that share these rows.
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < T; ++i) {
     float val = mx[i];
     val = fmaxf(val, __shfl_xor(val, 1));
     val = fmaxf(val, __shfl_xor(val, 2));
@@ -299,7 +323,7 @@ __global__ __launch_bounds__(kUpThreads) void upsample_kernel(
   }
   if (tx == 0) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < T; ++i)
       if (rbase + i < n) atomicMax(&rmax[rbase + i], __float_as_uint(mx[i]));
   }
 }
@@ -334,23 +358,36 @@ __global__ __launch_bounds__(64 * kScanWaves) void scan_kernel(
   uint32_t* dst_row = codes + (panel * n_chunks * kPanel + lane) * WORDS_PER_CHUNK;
   float u = 0.0f;
   int64_t wj = (gb * m_up) / PER_WORD;  // first word of this block in the row
+  // The samples of the next word are loaded while this word's are scanned: the
+  // scan is one dependent chain per lane, and a few panels (one block of a
+  // compensated encoding) leave nothing else to hide the loads (4096 rows, one
+  // block of 512 samples: 32 us with the loads in front of their use, 18.6 so).
+  float x[PER_WORD], xn[PER_WORD];
+#pragma unroll
+  for (int q = 0; q < PER_WORD; ++q) x[q] = live ? src[static_cast<int64_t>(q) * kPanel] : 0.0f;
   for (int m0 = 0; m0 < m_up; m0 += PER_WORD, ++wj) {
     uint32_t word = 0u;
+    const int mn = m0 + PER_WORD < m_up ? m0 + PER_WORD : m0;
+#pragma unroll
+    for (int q = 0; q < PER_WORD; ++q) xn[q] = live ? src[static_cast<int64_t>(mn + q) * kPanel] : 0.0f;
     if (live) {
-#pragma unroll 8
+      // (u - c s for c = +-1, 0: the same as subtracting the product c s)
+#pragma unroll
       for (int q = 0; q < PER_WORD; ++q) {
-        const float x = src[static_cast<int64_t>(m0 + q) * kPanel];
-        const float vv = u + x;
-        int c;
-        if (LEVELS == 3) c = (vv > theta) ? 1 : ((vv < -theta) ? -1 : 0);
-        else c = (vv >= 0.0f) ? 1 : -1;
-        const float cs = static_cast<float>(c) * s;
-        u = vv - cs;
-        uint32_t f;
-        if (LEVELS == 3) f = c == 0 ? 0u : (c > 0 ? 1u : 3u);
-        else f = c > 0 ? 1u : 0u;
-        word |= f << (BITS * q);
+        const float vv = u + x[q];
+        const float dn = vv - s, up = vv + s;
+        if (LEVELS == 3) {
+          const bool pos = vv > theta, neg = vv < -theta;
+          u = pos ? dn : (neg ? up : vv);
+          word |= pos ? 1u << (BITS * q) : (neg ? 3u << (BITS * q) : 0u);
+        } else {
+          const bool pos = vv >= 0.0f;
+          u = pos ? dn : up;
+          word |= pos ? 1u << q : 0u;
+        }
       }
+#pragma unroll
+      for (int q = 0; q < PER_WORD; ++q) x[q] = xn[q];
     }
     const int64_t c = wj / WORDS_PER_CHUNK;
     dst_row[c * kPanel * WORDS_PER_CHUNK + (wj % WORDS_PER_CHUNK)] = word;
@@ -531,8 +568,8 @@ sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t*
   return SDQ_OK;
 }
 
-sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t nbl,
-                                const sdq_layout* L, const Tables* T, void* codes, float* scales,
+template <typename W>
+static sdq_status encode_blocks(const W* w, int64_t ldw, int64_t b0, int64_t nbl, const sdq_layout* L, const Tables* T, void* codes, float* scales,
                                 const QuantWs& ws, uint32_t* rmax_acc, const uint32_t* rmax_scale,
                                 hipStream_t stream) {
   const int64_t n_panels = L->n_pad / kPanel;
@@ -545,7 +582,7 @@ sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t
   for (int i = 0; i < 8; ++i) sm.w[i] = L->hadamard == SDQ_HAD_SIGNED ? L->had_signs[i] : 0u;
   const dim3 rgrid(static_cast<unsigned>(n_ws / kPanel), static_cast<unsigned>(nbl));
 #define SDQ_ROT(BB)                                                                                 \
-  rotate_kernel<BB><<<rgrid, dim3(kRotThreads), 0, stream>>>(                                       \
+  rotate_kernel<BB, W><<<rgrid, dim3(kRotThreads), 0, stream>>>(                                       \
       w, L->n, ldw, n_ws, k_up, L->m_up, T->g0, T->phases, L->hadamard, sm, inv_sqrt_b, ws.v, ws.xup, \
       rmax_acc, ws.flag)
   switch (B) {
@@ -555,9 +592,13 @@ sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t
   }
 #undef SDQ_ROT
   if (T->m_nz > 0) {
-    const dim3 ugrid(static_cast<unsigned>(n_ws / kUpBM),
-                     static_cast<unsigned>(T->m_nz_pad / kUpBN), static_cast<unsigned>(nbl));
-    upsample_kernel<<<ugrid, dim3(kUpThreads), 0, stream>>>(
+    // The small tile below kUpSmall workgroups of the large one.
+    const bool small = n_ws / kUpBM * (T->m_nz_pad / kUpBN) * nbl < kUpSmall;
+    const int f = small ? 2 : 1;
+    const dim3 ugrid(static_cast<unsigned>(f * n_ws / kUpBM),
+                     static_cast<unsigned>(f * T->m_nz_pad / kUpBN), static_cast<unsigned>(nbl));
+    auto up = small ? upsample_kernel<4> : upsample_kernel<8>;
+    up<<<ugrid, dim3(kUpThreads), 0, stream>>>(
         ws.v, T->unz, L->n, n_ws, k_up, B, L->m_up, T->phases, T->m_nz, T->m_nz_pad, ws.xup,
         rmax_acc);
   }
@@ -573,6 +614,18 @@ sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "encoder launch");
   return SDQ_OK;
+}
+
+sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t nbl, const sdq_layout* L,
+                                const Tables* T, void* codes, float* scales, const QuantWs& ws,
+                                uint32_t* rmax_acc, const uint32_t* rmax_scale, hipStream_t stream) {
+  return encode_blocks(w, ldw, b0, nbl, L, T, codes, scales, ws, rmax_acc, rmax_scale, stream);
+}
+
+sdq_status launch_encode_blocks(const double* w, int64_t ldw, int64_t b0, int64_t nbl, const sdq_layout* L,
+                                const Tables* T, void* codes, float* scales, const QuantWs& ws,
+                                uint32_t* rmax_acc, const uint32_t* rmax_scale, hipStream_t stream) {
+  return encode_blocks(w, ldw, b0, nbl, L, T, codes, scales, ws, rmax_acc, rmax_scale, stream);
 }
 
 void clear_rmax(const QuantWs& ws, const sdq_layout* L, hipStream_t stream) {

@@ -100,10 +100,14 @@ sdq_status launch_repack_base3(const uint32_t* fields, const sdq_layout* L, void
 // The inverse: 2-bit fields (fields_view(L)) from base-3 codes.
 sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t* fields, hipStream_t stream);
 // Encode blocks b0 .. b0 + nbl - 1 from w (row stride ldw; column 0 of w is the
-// first column of block b0): rotate and upsample fold their row maxima into
+// first column of block b0; fp64 weights are rounded to fp32): rotate and upsample fold their row maxima into
 // rmax_acc, the scan uses the row scales in rmax_scale (one buffer for a plain
 // encode; a scratch buffer and the fixed scales for a re-encoded block).
 sdq_status launch_encode_blocks(const float* w, int64_t ldw, int64_t b0, int64_t nbl,
+                                const sdq_layout* L, const Tables* T, void* codes, float* scales,
+                                const QuantWs& ws, uint32_t* rmax_acc, const uint32_t* rmax_scale,
+                                hipStream_t stream);
+sdq_status launch_encode_blocks(const double* w, int64_t ldw, int64_t b0, int64_t nbl,
                                 const sdq_layout* L, const Tables* T, void* codes, float* scales,
                                 const QuantWs& ws, uint32_t* rmax_acc, const uint32_t* rmax_scale,
                                 hipStream_t stream);
