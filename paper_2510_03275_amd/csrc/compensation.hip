@@ -11,7 +11,7 @@
 //            columns: block b is rounded to fp32 and encoded with those
 //            scales (the same rotate / upsample / scan kernels), its
 //            reconstruction Q_b = (s * C_b) E^T (E = Had D^T, the table of the
-//            activation expansion, in fp64) gives the error E_b = W_b - Q_b, and
+//            activation expansion, in fp64, against the packed codes) gives the error E_b = W_b - Q_b, and
 //            the later columns are corrected with GPTQ's block step without its
 //            column-wise part, W_F -= E_b diag(U_QQ)^-1 U_QF (each column's
 //            error divided by its pivot), or optionally with the
@@ -37,6 +37,9 @@ namespace {
 constexpr int kT = 64;     // factorisation panel / GEMM tile
 constexpr int kTK = 16;    // GEMM k step
 constexpr int kStage = kT * kTK / 256;   // operand elements staged per thread and k step
+// Triangular operands of a GEMM: their zeros are left out of the K range.
+constexpr int kTriB = 1;   // B[p][j] = 0 for p < j
+constexpr int kTriA = 2;   // A[i][p] = 0 for p > i
 
 // Cholesky factor and inverse of one 64 x 64 block in place: the lower part
 // of A (row stride lda, unit column stride) is read, A = L L^T is written back
@@ -166,9 +169,9 @@ __global__ __launch_bounds__(256) void chol64_kernel(double* A, int64_t lda, dou
 }
 
 // C = beta C + alpha A B; element (i, p) of A at A[i * rsa + p * csa], likewise
-// B and C; blockIdx.z selects a batch (strides bsa, bsb, bsc).  lower_only = 1
-// skips tiles strictly above the diagonal of C; lower_only = 2 (a symmetric
-// product, M = N) skips them too but also updates the transposed position of
+// B and C; blockIdx.z selects a batch (strides bsa, bsb, bsc).  lower_only = 1 (M = N)
+// covers only the tiles on or below the diagonal of C; lower_only = 2 (a symmetric
+// product) does too but also updates the transposed position of
 // every tile below the diagonal, so both triangles are written.  beta == 0
 // never reads C.  A and B
 // may overlap C only where every output tile depends on the same rows of A
@@ -187,47 +190,80 @@ template <typename TA, typename TB, bool kChol = false>
 __global__ __launch_bounds__(256) void gemm64_kernel(
     int64_t M, int64_t N, int64_t K, double alpha, const TA* A, int64_t rsa, int64_t csa,
     int64_t bsa, const TB* B, int64_t rsb, int64_t csb, int64_t bsb, double beta, double* C,
-    int64_t rsc, int64_t csc, int64_t bsc, int lower_only, double* cx, int64_t ldx, int* info) {
+    int64_t rsc, int64_t csc, int64_t bsc, int lower_only, int tri, double* cx, int64_t ldx, int* info) {
   __shared__ double As[kTK][kT + 2];
   __shared__ double Bs[kTK][kT + 2];
   const int tid = threadIdx.x;
   const int lane = tid % 64, wave = tid / 64;
   const int wr = wave / 2, wc = wave % 2;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kT;
-  const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kT;
-  if (lower_only && i0 + kT - 1 < j0) return;
+  int64_t ty = blockIdx.y, tx = blockIdx.x;
+  if (lower_only) {
+    // A one-dimensional grid over the tiles on or below the diagonal, row by row,
+    // each XCD a contiguous range (workgroups go to the eight XCDs in turn, each
+    // with its own L2).  A square grid whose upper half returned at once gave
+    // the XCDs and CUs unequal shares.
+    const int64_t g = gridDim.x, xcd = tx % 8;
+    const int64_t t = xcd * (g / 8) + min<int64_t>(xcd, g % 8) + tx / 8;
+    ty = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(t) + 1.0) - 1.0) * 0.5);
+    while ((ty + 1) * (ty + 2) / 2 <= t) ++ty;
+    while (ty * (ty + 1) / 2 > t) --ty;
+    tx = t - ty * (ty + 1) / 2;
+  } else if (tri == kTriB && (ty / 8) % 2) {
+    // Triangular B: the K range shrinks along a row of tiles, and a CU gets every
+    // eighth row of one column (256 CUs, eight XCDs); every other eight rows run
+    // backwards, which evens the CUs out (2048-blocks: 349 us without the K
+    // ranges, 221 with them; without this order they gained nothing).
+    tx = gridDim.x - 1 - tx;
+  }
+  const int64_t i0 = ty * kT, j0 = tx * kT;
   A += static_cast<int64_t>(blockIdx.z) * bsa;
   B += static_cast<int64_t>(blockIdx.z) * bsb;
   C += static_cast<int64_t>(blockIdx.z) * bsc;
+  const int64_t kb = tri == kTriB ? j0 : 0;                          // K range (j0, i0: multiples of the slice)
+  const int64_t ke = tri == kTriA ? min<int64_t>(K, i0 + kT) : K;
   // Staging: element e = tid + 256 q of the slice, consecutive threads along
   // the operand's contiguous index.
   const bool a_pfast = csa == 1;
   const bool b_jfast = csb == 1;
-  int aii[kStage], app[kStage], bjj[kStage], bpp[kStage];
+  // Element q of a thread: row ai + q aii at p = ap + q api (and likewise B).  Loads
+  // are unconditional, from clamped places: rows and columns past the matrix
+  // feed outputs that are not stored, and what lies past K is stored as zero.
+  const int ap = a_pfast ? tid % kTK : tid / kT, ai = a_pfast ? tid / kTK : tid % kT;
+  const int bp = b_jfast ? tid / kT : tid % kTK, bj = b_jfast ? tid % kT : tid / kTK;
+  const int api = a_pfast ? 0 : 4, aii = a_pfast ? 16 : 0;
+  const int bpi = b_jfast ? 4 : 0, bji = b_jfast ? 0 : 16;
+  const TA* ag[kStage];
+  const TB* bg[kStage];
 #pragma unroll
   for (int q = 0; q < kStage; ++q) {
-    const int e = tid + 256 * q;
-    aii[q] = a_pfast ? e / kTK : e % kT;
-    app[q] = a_pfast ? e % kTK : e / kT;
-    bjj[q] = b_jfast ? e % kT : e / kTK;
-    bpp[q] = b_jfast ? e / kT : e % kTK;
+    ag[q] = A + min<int64_t>(i0 + ai + q * aii, M - 1) * rsa + (kb + min<int64_t>(ap + q * api, K - 1 - kb)) * csa;
+    bg[q] = B + min<int64_t>(j0 + bj + q * bji, N - 1) * csb + (kb + min<int64_t>(bp + q * bpi, K - 1 - kb)) * rsb;
   }
   TA ra[kStage];
   TB rb[kStage];
   auto load = [&](int64_t p0) {
+    if (p0 + kTK <= K) {
 #pragma unroll
-    for (int q = 0; q < kStage; ++q) {
-      const int64_t gi = i0 + aii[q], gp = p0 + app[q];
-      ra[q] = gi < M && gp < K ? A[gi * rsa + gp * csa] : TA(0);
-      const int64_t gj = j0 + bjj[q], gq = p0 + bpp[q];
-      rb[q] = gj < N && gq < K ? B[gq * rsb + gj * csb] : TB(0);
+      for (int q = 0; q < kStage; ++q) {
+        ra[q] = ag[q][(p0 - kb) * csa];
+        rb[q] = bg[q][(p0 - kb) * rsb];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kStage; ++q) {   // a last, partial slice
+        const bool av = p0 + ap + q * api < K, bv = p0 + bp + q * bpi < K;
+        ra[q] = ag[q][av ? (p0 - kb) * csa : 0];
+        rb[q] = bg[q][bv ? (p0 - kb) * rsb : 0];
+        ra[q] = av ? ra[q] : TA(0);
+        rb[q] = bv ? rb[q] : TB(0);
+      }
     }
   };
   auto store = [&]() {
 #pragma unroll
     for (int q = 0; q < kStage; ++q) {
-      As[app[q]][aii[q]] = static_cast<double>(ra[q]);
-      Bs[bpp[q]][bjj[q]] = static_cast<double>(rb[q]);
+      As[ap + q * api][ai + q * aii] = static_cast<double>(ra[q]);
+      Bs[bp + q * bpi][bj + q * bji] = static_cast<double>(rb[q]);
     }
   };
   double4_t acc[2][2];
@@ -236,11 +272,11 @@ __global__ __launch_bounds__(256) void gemm64_kernel(
 #pragma unroll
     for (int c = 0; c < 2; ++c) acc[r][c] = double4_t{0.0, 0.0, 0.0, 0.0};
   const int lr = lane % 16, lk = lane / 16;
-  load(0);
+  load(kb);
   store();
   __syncthreads();
-  for (int64_t p0 = 0; p0 < K; p0 += kTK) {
-    const bool more = p0 + kTK < K;
+  for (int64_t p0 = kb; p0 < ke; p0 += kTK) {
+    const bool more = p0 + kTK < ke;
     if (more) load(p0 + kTK);
 #pragma unroll
     for (int kk = 0; kk < kTK / 4; ++kk) {
@@ -283,11 +319,106 @@ __global__ __launch_bounds__(256) void gemm64_kernel(
   if constexpr (kChol) {
     // The first tile goes on to its Cholesky factor and inverse (the tile's
     // stores above are visible to the whole workgroup after the barrier).
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
+    if (i0 == 0 && j0 == 0) {
       __syncthreads();
       chol64_tile(C, rsc, cx, ldx, info, &As[0][0]);
     }
   }
+}
+
+// The block error of the compensated encoder straight from the codes and the
+// weights: E = W_b - (s C_b) Eb^T with C_b the packed codes of samples j0 .. j0 + M - 1
+// (M a multiple of 32, j0 too: a 16-deep slice is one ternary word or half a
+// binary one) and Eb the B x M table; out[r][t] = E[r][t] / u[t][t] (kDiv) or
+// E[r][t].  64 x 64 tile, the loop of gemm64_kernel: the codes are decoded into
+// the LDS slice, so the scaled codes, the copy of the block and the division
+// take no pass of their own (61 us of passes and product per block of 4096 rows
+// and 512 samples before, 33 so; 16 us at the matrix cores' 77 TFLOP/s, but one
+// workgroup per CU shows the latency of its loads, here two slices ahead).
+template <int BITS>
+__global__ __launch_bounds__(256) void block_error_kernel(
+    const uint32_t* __restrict__ codes, const float* __restrict__ scales, int64_t n, int64_t n_chunks, int64_t j0s,
+    int64_t M, const double* __restrict__ e64, const double* __restrict__ w, int64_t ldw, int B,
+    const double* __restrict__ u, int64_t ldu, double* __restrict__ out) {
+  __shared__ double As[2][kTK][kT + 2];
+  __shared__ double Bs[2][kTK][kT + 2];
+  const int tid = threadIdx.x;
+  const int lane = tid % 64, wave = tid / 64;
+  const int wr = wave / 2, wc = wave % 2;
+  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kT;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kT;
+  // Codes: thread t decodes samples 4 (t % 4) .. + 3 of row t / 4; the table:
+  // sample t % 16 of rows t / 16 + 16 q.  Rows past n have codes of 0 (padding) or
+  // are not stored.
+  const int64_t row = min<int64_t>(i0 + tid / 4, n - 1);
+  const double s = static_cast<double>(scales[row]);
+  const uint32_t* crow = codes + ((row / kPanel) * n_chunks * kPanel + row % kPanel) * 4;
+  const double* eb = e64 + (t0 + tid / 16) * M + tid % 16;
+  uint32_t word[2];
+  double rb[2][4];
+  auto load = [&](int set, int64_t p) {
+    const int64_t p0 = min<int64_t>(p, M - kTK);               // (a slice past the end is not multiplied)
+    const int64_t bit = (j0s + p0) * BITS;                     // of the row's code string
+    const int64_t wi = bit / 32;
+    word[set] = crow[(wi / 4) * kPanel * 4 + wi % 4] >> (bit % 32);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rb[set][q] = eb[p0 + 16 * q * M];
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t f = (word[buf] >> (BITS * (4 * (tid % 4) + q))) & ((1u << BITS) - 1u);
+      const double code = BITS == 1 ? (f ? 1.0 : -1.0) : (f == 1u ? 1.0 : (f == 3u ? -1.0 : 0.0));
+      As[buf][4 * (tid % 4) + q][tid / 4] = s * code;
+      Bs[buf][tid % 16][tid / 16 + 16 * q] = rb[buf][q];
+    }
+  };
+  double4_t acc[2][2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) acc[r][c] = double4_t{0.0, 0.0, 0.0, 0.0};
+  const int lr = lane % 16, lk = lane / 16;
+  auto slice = [&](int cur, int64_t p0) {
+    load(cur, p0 + 2 * kTK);
+#pragma unroll
+    for (int kk = 0; kk < kTK / 4; ++kk) {
+      double a[2], b[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) a[r] = As[cur][4 * kk + lk][32 * wr + 16 * r + lr];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) b[c] = Bs[cur][4 * kk + lk][32 * wc + 16 * c + lr];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[c], acc[r][c], 0, 0, 0);
+    }
+    store(cur ^ 1);
+    __syncthreads();
+  };
+  load(0, 0);
+  load(1, kTK);
+  store(0);
+  __syncthreads();
+  for (int64_t p0 = 0; p0 < M; p0 += 2 * kTK) {    // M is a multiple of 32
+    slice(0, p0);
+    slice(1, p0 + kTK);
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int64_t t = t0 + 32 * wc + 16 * c + lr;
+      const double piv = u ? u[t * ldu + t] : 1.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t gi = i0 + 32 * wr + 16 * r + lk + 4 * v;
+        if (gi < n) {
+          const double e = w[gi * ldw + t] - acc[r][c][v];
+          out[gi * B + t] = u ? e / piv : e;
+        }
+      }
+    }
 }
 
 // Inverse X = L^-1 of lower-triangular 64 x 64 diagonal blocks, one per
@@ -375,62 +506,22 @@ __global__ void widen_kernel(const float* __restrict__ w, int64_t count, double*
     w64[i] = static_cast<double>(w[i]);
 }
 
-// Block column col0 .. col0 + B - 1 of W64 (n x k): rounded to fp32 into wblk
-// (n x B, the encoder's input) and copied into ebuf (n x B, fp64).
-__global__ void extract_block_kernel(const double* __restrict__ w64, int64_t n, int64_t k, int B,
-                                     int64_t col0, float* __restrict__ wblk, double* __restrict__ ebuf) {
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < n * B;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t r = e / B, t = e % B;
-    const double v = w64[r * k + col0 + t];
-    wblk[e] = static_cast<float>(v);
-    ebuf[e] = v;
-  }
-}
-
-// cb[r][m] = s_r * code(r, j0 + m) (n x M, fp64) from the packed format.
-__global__ void unpack_scaled_kernel(const uint32_t* __restrict__ codes, const float* __restrict__ scales,
-                                     int64_t n, int64_t n_chunks, int cpc, int bits, int64_t j0,
-                                     int m_up, double* __restrict__ cb) {
-  const int per_word = 32 / bits;
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < n * m_up;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t r = e / m_up;
-    const int64_t j = j0 + e % m_up;
-    const int64_t c = j / cpc;
-    const int q = static_cast<int>(j % cpc);
-    const uint32_t word = codes[(((r / kPanel) * n_chunks + c) * kPanel + r % kPanel) * 4 + q / per_word];
-    const uint32_t f = (word >> (bits * (q % per_word))) & ((1u << bits) - 1u);
-    const double code = bits == 1 ? (f ? 1.0 : -1.0) : (f == 1u ? 1.0 : (f == 3u ? -1.0 : 0.0));
-    cb[e] = static_cast<double>(scales[r]) * code;
-  }
-}
-
-// g[r][t] = e[r][t] / u[c0 + t][c0 + t] (n x B): the block error of every
-// column divided by that column's pivot, an IEEE division per element.
-__global__ void divide_by_pivots_kernel(const double* __restrict__ e, const double* __restrict__ u,
-                                        int64_t k, int64_t c0, int64_t n, int B, double* __restrict__ g) {
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n * B;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t t = c0 + i % B;
-    g[i] = e[i] / u[t * k + t];
-  }
-}
-
 unsigned grid1(int64_t count) {
   return static_cast<unsigned>(std::min<int64_t>((count + 255) / 256, 8192));
 }
 
+// lower_only as for the kernel; tri: kTriA, kTriB or 0.
 template <typename TA, typename TB>
 void gemm64(int64_t M, int64_t N, int64_t K, double alpha, const TA* A, int64_t rsa, int64_t csa,
             const TB* B, int64_t rsb, int64_t csb, double beta, double* C, int64_t rsc, int64_t csc,
             hipStream_t stream, int lower_only = 0, int batch = 1, int64_t bsa = 0, int64_t bsb = 0,
-            int64_t bsc = 0) {
+            int64_t bsc = 0, int tri = 0) {
   if (M <= 0 || N <= 0) return;
-  const dim3 grid(static_cast<unsigned>((N + kT - 1) / kT), static_cast<unsigned>((M + kT - 1) / kT),
+  const int64_t by = (M + kT - 1) / kT, bx = (N + kT - 1) / kT;
+  const dim3 grid(static_cast<unsigned>(lower_only ? by * (by + 1) / 2 : bx), static_cast<unsigned>(lower_only ? 1 : by),
                   static_cast<unsigned>(batch));
   gemm64_kernel<TA, TB><<<grid, dim3(256), 0, stream>>>(M, N, K, alpha, A, rsa, csa, bsa, B, rsb, csb,
-                                                        bsb, beta, C, rsc, csc, bsc, lower_only, nullptr, 0,
+                                                        bsb, beta, C, rsc, csc, bsc, lower_only, tri, nullptr, 0,
                                                         nullptr);
 }
 
@@ -440,10 +531,10 @@ void gemm64(int64_t M, int64_t N, int64_t K, double alpha, const TA* A, int64_t 
 // (L into C's first tile, its inverse into X).
 void trailing_update_chol(int64_t n, const double* P, double* C, int64_t ld, double* X, int64_t ldx, int* info,
                           hipStream_t stream) {
-  const unsigned tiles = static_cast<unsigned>((n + kT - 1) / kT);
-  gemm64_kernel<double, double, true><<<dim3(tiles, tiles, 1), dim3(256), 0, stream>>>(
-      n, n, int64_t{kT}, -1.0, P, ld, int64_t{1}, 0, P, int64_t{1}, ld, 0, 1.0, C, ld, int64_t{1}, 0, 1, X,
-      ldx, info);
+  const int64_t tiles = (n + kT - 1) / kT;
+  gemm64_kernel<double, double, true><<<dim3(static_cast<unsigned>(tiles * (tiles + 1) / 2)), dim3(256), 0, stream>>>(
+      n, n, int64_t{kT}, -1.0, P, ld, int64_t{1}, 0, P, int64_t{1}, ld, 0, 1.0, C, ld, int64_t{1}, 0, 1, 0,
+      X, ldx, info);
 }
 
 // Lower-triangular inverse X = L^-1 of a batch of n x n matrices (n a multiple
@@ -462,9 +553,9 @@ void trtri_pow2(const double* L, double* X, int64_t n, int64_t ld, int64_t s, in
     const int64_t ps = 2 * b * (ld + 1);                  // diagonal step between pairs
     auto join = [&](int64_t off, int nbat, int64_t mstride) {
       gemm64(b, b, b, 1.0, L + off + b * ld, ld, int64_t{1}, X + off, ld, int64_t{1}, 0.0, tmp, b,
-             int64_t{1}, stream, 0, nbat, mstride, mstride, b * b);
+             int64_t{1}, stream, 0, nbat, mstride, mstride, b * b, kTriB);
       gemm64(b, b, b, -1.0, X + off + b * ld + b, ld, int64_t{1}, tmp, b, int64_t{1}, 0.0, X + off + b * ld,
-             ld, int64_t{1}, stream, 0, nbat, mstride, b * b, mstride);
+             ld, int64_t{1}, stream, 0, nbat, mstride, b * b, mstride, kTriA);
     };
     if (batch == 1) {
       join(0, static_cast<int>(pairs), ps);
@@ -486,9 +577,9 @@ void trtri_lower(const double* L, double* X, int64_t n, int64_t ld, int64_t s, i
   trtri_pow2(L, X, n1, ld, s, batch, tmp, stream);
   trtri_lower(L + n1 * (ld + 1), X + n1 * (ld + 1), n2, ld, s, batch, tmp, stream);
   gemm64(n2, n1, n1, 1.0, L + n1 * ld, ld, int64_t{1}, X, ld, int64_t{1}, 0.0, tmp, n1, int64_t{1}, stream, 0,
-         batch, s, s, n2 * n1);
+         batch, s, s, n2 * n1, kTriB);
   gemm64(n2, n1, n2, -1.0, X + n1 * ld + n1, ld, int64_t{1}, tmp, n1, int64_t{1}, 0.0, X + n1 * ld, ld,
-         int64_t{1}, stream, 0, batch, s, n2 * n1, s);
+         int64_t{1}, stream, 0, batch, s, n2 * n1, s, kTriA);
 }
 
 }  // namespace
@@ -539,18 +630,16 @@ sdq_status launch_hessian_factor(const double* h, int64_t k, double lam, double*
 }
 
 // Workspace of the compensated encoder: the plain encoder's, then (256-byte
-// aligned) scratch row maxima, W64 (n x k), the fp32 block (n x B), E and G
-// (n x B each), the scaled codes (n x M), and per block the reversed diagonal
+// aligned) scratch row maxima, W64 (n x k), E and G (n x B each), and per block
+// the reversed diagonal
 // block of U, its inverse, the inverse reversed back (nb x B x B each) and
 // the triangular-inverse scratch (nb x 64 x B).
 struct CompWs {
   QuantWs q;
   uint32_t* rmax_scratch;
   double* w64;
-  float* wblk;
   double* ebuf;
   double* gbuf;
-  double* cb;
   double* lb;
   double* xb;
   double* vb;
@@ -570,10 +659,8 @@ size_t comp_ws_layout(const sdq_layout* L, CompWs* out, void* base) {
   const size_t n = static_cast<size_t>(L->n), B = static_cast<size_t>(L->block), nb = static_cast<size_t>(L->nb);
   w.rmax_scratch = reinterpret_cast<uint32_t*>(take(static_cast<size_t>(L->n_pad) * 4));
   w.w64 = reinterpret_cast<double*>(take(n * L->k * 8));
-  w.wblk = reinterpret_cast<float*>(take(n * B * 4));
   w.ebuf = reinterpret_cast<double*>(take(n * B * 8));
   w.gbuf = reinterpret_cast<double*>(take(n * B * 8));
-  w.cb = reinterpret_cast<double*>(take(n * L->m_up * 8));
   w.lb = reinterpret_cast<double*>(take(nb * B * B * 8));
   w.xb = reinterpret_cast<double*>(take(nb * B * B * 8));
   w.vb = reinterpret_cast<double*>(take(nb * B * B * 8));
@@ -616,26 +703,27 @@ sdq_status launch_quantize_compensated(const float* w, const sdq_layout* L, cons
   // 3. The walk over the blocks, W in fp64.
   widen_kernel<<<grid1(n * k), 256, 0, stream>>>(w, n * k, cw.w64);
   for (int64_t b = 0; b < nb; ++b) {
-    extract_block_kernel<<<grid1(n * B), 256, 0, stream>>>(cw.w64, n, k, static_cast<int>(B), b * B,
-                                                           cw.wblk, cw.ebuf);
-    if (b > 0) {
-      st = launch_encode_blocks(cw.wblk, B, b, 1, F, T, fcodes, scales, cw.q, cw.rmax_scratch,
+    if (b > 0) {   // the block of W64, rounded to fp32
+      st = launch_encode_blocks(cw.w64 + b * B, k, b, 1, F, T, fcodes, scales, cw.q, cw.rmax_scratch,
                                 cw.q.rmax, stream);
       if (st != SDQ_OK) return st;
     }
     if (b == nb - 1) break;
-    unpack_scaled_kernel<<<grid1(n * M), 256, 0, stream>>>(static_cast<const uint32_t*>(fcodes), scales, n,
-                                                           F->n_chunks, F->codes_per_chunk, F->bits,
-                                                           b * M, static_cast<int>(M), cw.cb);
-    // E_b = W_b - (s C_b) E^T
-    gemm64(n, B, M, -1.0, cw.cb, M, int64_t{1}, T->e64, int64_t{1}, M, 1.0, cw.ebuf, B, int64_t{1}, stream);
-    if (joint) {      // G = E_b V_b
+    // E_b = W_b - (s C_b) E^T, and G = E_b diag(U_bb)^-1 or (joint) G = E_b V_b
+    double* err = joint ? cw.ebuf : cw.gbuf;
+    const double* piv = joint ? nullptr : u + b * B * k + b * B;
+    const dim3 egrid(static_cast<unsigned>(B / kT), static_cast<unsigned>((n + kT - 1) / kT));
+    if (F->bits == 1)
+      block_error_kernel<1><<<egrid, 256, 0, stream>>>(static_cast<const uint32_t*>(fcodes), scales, n, F->n_chunks,
+                                                       b * M, M, T->e64, cw.w64 + b * B, k, static_cast<int>(B),
+                                                       piv, k, err);
+    else
+      block_error_kernel<2><<<egrid, 256, 0, stream>>>(static_cast<const uint32_t*>(fcodes), scales, n, F->n_chunks,
+                                                       b * M, M, T->e64, cw.w64 + b * B, k, static_cast<int>(B),
+                                                       piv, k, err);
+    if (joint)
       gemm64(n, B, B, 1.0, cw.ebuf, B, int64_t{1}, cw.vb + b * bb, B, int64_t{1}, 0.0, cw.gbuf, B, int64_t{1},
              stream);
-    } else {          // G = E_b diag(U_bb)^-1
-      divide_by_pivots_kernel<<<grid1(n * B), 256, 0, stream>>>(cw.ebuf, u, k, b * B, n, static_cast<int>(B),
-                                                               cw.gbuf);
-    }
     // W_F -= G U[Q, F]
     const int64_t f0 = (b + 1) * B;
     gemm64(n, k - f0, B, -1.0, cw.gbuf, B, int64_t{1}, u + b * B * k + f0, k, int64_t{1}, 1.0, cw.w64 + f0, k,
