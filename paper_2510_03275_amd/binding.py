@@ -124,6 +124,29 @@ def _load() -> ctypes.CDLL:
 
 _lib = _load()
 
+import torch  # noqa: E402  (after the library: _load imports it first)
+
+# The per-token entry points as native calls (csrc/pycall.c), else through
+# ctypes: fn(*integers).
+def _native_calls():
+    names = ("sdq_linear", "sdq_linear_group", "sdq_linear_workspace_bytes")
+    try:
+        from . import _sdqcall
+    except ImportError:
+        fns = []
+        for name in names:        # prototypes of their own: layouts and arrays by address
+            src = getattr(_lib, name)
+            pointers = [ctypes.c_void_p if issubclass(t, ctypes._Pointer) else t for t in src.argtypes]
+            fns.append(ctypes.CFUNCTYPE(src.restype, *pointers)((name, _lib)))
+        return fns
+    _sdqcall.bind(*(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
+    return _sdqcall.linear, _sdqcall.linear_group, _sdqcall.linear_workspace_bytes
+
+
+_call_linear, _call_group, _call_workspace = _native_calls()
+_addr = ctypes.addressof
+_DTYPES = {torch.float16: SDQ_F16, torch.bfloat16: SDQ_BF16, torch.float32: SDQ_F32}
+
 
 def lib() -> ctypes.CDLL:
     return _lib
@@ -138,16 +161,21 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream (1.5 us), where
+# this torch offers it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None) -> Optional[int]:
-    import torch
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 
 def _dtype_code(t) -> int:
-    import torch
-    return {torch.float16: SDQ_F16, torch.bfloat16: SDQ_BF16, torch.float32: SDQ_F32}[t.dtype]
+    return _DTYPES[t.dtype]
 
 
 # ---------------------------------------------------------------------------
@@ -205,11 +233,13 @@ def sdq_linear_workspace_bytes(layout: sdq_layout, m: int) -> int:
 
 def sdq_linear(x, codes, scales, layout: sdq_layout, y, workspace, stream=None,
                accumulate: bool = False) -> None:
-    m = x.shape[0] if x.dim() == 2 else 0
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(_lib.sdq_linear(_ptr(x), _dtype_code(x), m, _ptr(codes), _ptr(scales),
-                           ctypes.byref(layout), _ptr(y), int(bool(accumulate)), _ptr(workspace),
-                           ws_bytes, _stream(stream)))
+    shape = x.shape
+    status = _call_linear(x.data_ptr(), _DTYPES[x.dtype], shape[0] if len(shape) == 2 else 0,
+                          None if codes is None else codes.data_ptr(), None if scales is None else scales.data_ptr(),
+                          _addr(layout), None if y is None else y.data_ptr(), 1 if accumulate else 0,
+                          _ptr(workspace), _nbytes(workspace), _stream(stream))
+    if status != SDQ_OK:
+        _check(status)
 
 
 def _layout_array(layouts):
@@ -238,10 +268,12 @@ class LinearGroup:
 
 
 def sdq_linear_group(x, group: "LinearGroup", workspace, stream=None, accumulate: bool = False) -> None:
-    m = x.shape[0] if x.dim() == 2 else 0
-    _check(_lib.sdq_linear_group(_ptr(x), _dtype_code(x), m, group.count, group.codes, group.scales,
-                                 group.layouts, group.ys, int(bool(accumulate)), _ptr(workspace),
-                                 _nbytes(workspace), _stream(stream)))
+    shape = x.shape
+    status = _call_group(x.data_ptr(), _DTYPES[x.dtype], shape[0] if len(shape) == 2 else 0, group.count,
+                         _addr(group.codes), _addr(group.scales), _addr(group.layouts), _addr(group.ys),
+                         1 if accumulate else 0, _ptr(workspace), _nbytes(workspace), _stream(stream))
+    if status != SDQ_OK:
+        _check(status)
 
 
 def sdq_linear_group_expanded(m: int, group: "LinearGroup", workspace, stream=None,
@@ -275,7 +307,7 @@ def sdq_linear_expanded(m: int, codes, scales, layout: sdq_layout, y, workspace,
 
 
 def _nbytes(t) -> int:
-    return 0 if t is None else t.numel() * t.element_size()
+    return 0 if t is None else t.nbytes
 
 
 def sdq_hessian_accumulate(x, h, stream=None) -> None:
@@ -376,7 +408,6 @@ def quantize(w, osr: float, levels: int, block: int = 256, workspace=None, check
     ``hadamard`` / ``signs`` choose Had (see sdq_layout_set_hadamard);
     ``packing`` the code storage of a ternary layout (SDQ_PACK_BASE3: five
     codes per byte)."""
-    import torch
     if w.dtype != torch.float32 or not w.is_cuda or not w.is_contiguous():
         raise ValueError("w must be a contiguous fp32 device tensor")
     layout = sdq_layout_init(w.shape[0], w.shape[1], osr, levels, block)
@@ -397,7 +428,6 @@ def quantize(w, osr: float, levels: int, block: int = 256, workspace=None, check
 
 def hessian_factor(h, lam: float, check: bool = True, stream=None):
     """U = Cholesky((H + lam I)^-1)^T for a device fp64 [k, k] H; returns U (fp64, device)."""
-    import torch
     u = torch.empty_like(h)
     ws = torch.empty(sdq_hessian_factor_workspace_bytes(h.shape[0]), dtype=torch.uint8, device=h.device)
     sdq_hessian_factor(h, lam, u, ws, stream)
@@ -411,7 +441,6 @@ def quantize_compensated(w, osr: float, levels: int, u, block: int = 256, check:
                          packing: int = SDQ_PACK_FIELDS, update: int = SDQ_COMP_GPTQ) -> Encoded:
     """Encode a device fp32 weight [n, k] with Algorithm 1's block compensation (u: fp64 [k, k];
     ``update``: SDQ_COMP_GPTQ or SDQ_COMP_JOINT)."""
-    import torch
     if w.dtype != torch.float32 or not w.is_cuda or not w.is_contiguous():
         raise ValueError("w must be a contiguous fp32 device tensor")
     if u.dtype != torch.float64 or tuple(u.shape) != (w.shape[1], w.shape[1]) or not u.is_contiguous():
@@ -435,15 +464,16 @@ def linear(x, enc: Encoded, workspace=None, out=None, stream=None, accumulate: b
 
     With accumulate=True the product is added into `out` (which must be given).
     """
-    import torch
-    if not x.is_cuda or not x.is_contiguous() or x.dim() != 2 or x.shape[1] != enc.layout.k:
+    layout = enc.layout
+    shape = x.shape
+    if not x.is_cuda or not x.is_contiguous() or len(shape) != 2 or shape[1] != layout.k:
         raise ValueError("x must be a contiguous device tensor [m, k]")
-    m = x.shape[0]
+    m = shape[0]
     if accumulate and out is None:
         raise ValueError("accumulate=True needs out")
-    y = out if out is not None else torch.empty((m, enc.layout.n), dtype=torch.float32, device=x.device)
-    need = sdq_linear_workspace_bytes(enc.layout, m)
-    if workspace is None or workspace.numel() * workspace.element_size() < need:
+    y = out if out is not None else torch.empty((m, layout.n), dtype=torch.float32, device=x.device)
+    need = _call_workspace(_addr(layout), m)
+    if workspace is None or workspace.nbytes < need:
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x.device)
-    sdq_linear(x, enc.codes, enc.scales, enc.layout, y, workspace, stream, accumulate)
+    sdq_linear(x, enc.codes, enc.scales, layout, y, workspace, stream, accumulate)
     return y

@@ -14,6 +14,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -78,11 +79,32 @@ def _build_synth() -> str:
     return SYNTH_LIB
 
 
+PYCALL = os.path.join(HERE, "_sdqcall.so")
+
+
+def _build_pycall() -> None:
+    """The binding's native calls (csrc/pycall.c), where Python's headers are
+    installed; the binding uses ctypes without it."""
+    inc = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(inc, "Python.h")):
+        if os.path.exists(PYCALL):
+            os.remove(PYCALL)
+        return
+    tmp = PYCALL + ".tmp"
+    cmd = ["gcc", "-O2", "-fPIC", "-shared", "-Wall", f"-I{inc}", os.path.join(CSRC, "pycall.c"), "-o", tmp]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"pycall build failed: {' '.join(cmd)}\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, PYCALL)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, 8)) as ex:
         synth_job = ex.submit(_build_synth)
+        pycall_job = ex.submit(_build_pycall)
         objs = list(ex.map(_compile, SOURCES))
+        pycall_job.result()
         synth_job.result()
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
