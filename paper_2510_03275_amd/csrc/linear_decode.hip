@@ -1606,7 +1606,13 @@ bool mfma_lds(const sdq_layout* L, int64_t m, int64_t panels) {
 // 8192 x 8192, OSR 2): one block per wave is best up to two plane groups
 // (m <= 8) and on the LDS-shared launches; otherwise, from three plane groups
 // on, the longer-lived waves of two blocks each win (m = 16: 64 -> 56 us on
-// 28672 x 8192, 72 -> 59 us on 8192 x 28672; m = 12 o_proj 21.7 -> 19.5 us).
+// 28672 x 8192, 72 -> 59 us on 8192 x 28672; m = 12 o_proj 21.7 -> 19.5 us),
+// while launches whose workgroups at one block per wave all fit the chip at once
+// are short of waves: one against two blocks at m = 16, 256 workgroups (LLaMA-7B
+// o_proj, OSR 2.125) 9.2 against 12.2 us, 704 (down_proj, OSR 2.5) 17.6 against
+// 19.0, 768 (q/k/v, OSR 2.25) 17.6 against 22.5, but 1024 (8192 x 8192, OSR 3.25)
+// 31.0 against 25.8 and 1376 (gate/up) 31.4 against 29.4; at m = 12, 1024 still
+// 20.1 against 24.6, 1280 18.3 against 17.6.
 int mfma_bpw(const sdq_layout* L, int64_t m, int64_t panels) {
   static const char* env = std::getenv("SDQ_MFMA_BPW");
   if (env) {
@@ -1615,6 +1621,7 @@ int mfma_bpw(const sdq_layout* L, int64_t m, int64_t panels) {
   }
   const int npg = npg_for(m);
   if (npg <= 2) return 1;
+  if (panels * ((L->nb + 3) / 4) <= (npg == 3 ? 1024 : 768)) return 1;
   return npg == 3 && mfma_lds(L, m, panels) ? 1 : 2;
 }
 
