@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "sdq_internal.h"
 
@@ -49,17 +50,21 @@ constexpr int kTriA = 2;   // A[i][p] = 0 for p > i
 // it and subtracts m_i times row j from row i, in the reduced matrix and in a
 // copy of the identity, which becomes L'^-1 for the unit lower factor of
 // A = L' D L'^T.  Then column j of L is c / sqrt(d_j) and L^-1 = D^-1/2 L'^-1
-// (row i divided by sqrt(d_i)).  Thread t keeps a 4 x 4 tile of the reduced
-// matrix and of the inverse in registers (rows 4 (t / 16) .., columns
-// 4 (t % 16) ..; a finished column stays in place).  Per step, the owners of
-// the next column and of the next row of the inverse update those first and
-// publish them in a two-slot LDS ring, with the next-but-one diagonal entry;
-// from that entry every thread forms the next pivot and its reciprocal while
-// the rest of the tile is updated, so only a multiply and an FMA lie between
-// two barriers on the column-to-column path (one barrier per column).  Upper
-// entries of the tiles are updated too and never read.  A pivot that is not
-// positive sets *info and is taken as 1.  Needs 256 threads and 322 doubles of
-// LDS at lds.
+// (row i divided by sqrt(d_i)).  Thread t keeps a 4 x 4 sample of the reduced
+// matrix and of the inverse in registers: rows t / 16 + 16 r, columns t % 16 + 16 c.
+// So after each sixteen columns every thread is done with one of its rows and
+// columns, and together with the triangles (c <= r; the inverse up to column j)
+// 14, 12, 9 and 5 of its 32 elements are updated per step in the four phases (a
+// contiguous 4 x 4 tile: 32 throughout).  With it the trailing updates that end
+// in this, where it bounds them, went from 45-49 to 34 us (k = 4096, the last 40
+// of 63); what is left is the latency of each column's chain, about 0.4 us.  Per step, the owners of the next column and of the next row of the
+// inverse update those first and publish them in a two-slot LDS ring, with the
+// next-but-one diagonal entry; from that entry every thread forms the next pivot
+// and its reciprocal while the rest is updated, so only a multiply and an FMA lie
+// between two barriers on the column-to-column path (one barrier per column).
+// Upper entries of the diagonal samples are updated too and never read.  A pivot
+// that is not positive sets *info and is taken as 1.  Needs 256 threads and 322
+// doubles of LDS at lds.
 __device__ __forceinline__ void chol64_tile(double* A, int64_t lda, double* X, int64_t ldx, int* info,
                                             double* lds) {
   double(*ct)[kT] = reinterpret_cast<double(*)[kT]>(lds);            // column j in slot j % 2
@@ -68,25 +73,22 @@ __device__ __forceinline__ void chol64_tile(double* A, int64_t lda, double* X, i
   double* dv = lds + 4 * kT + 2;                                      // pivots
   const int tid = threadIdx.x;
   const int ti = tid / 16, tk = tid % 16;
-  const int i0 = 4 * ti, k0 = 4 * tk;
   double a[4][4], x[4][4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      a[r][c] = k0 + c <= i0 + r ? A[(i0 + r) * lda + k0 + c] : 0.0;
-      x[r][c] = i0 + r == k0 + c ? 1.0 : 0.0;
+      const int i = ti + 16 * r, k = tk + 16 * c;
+      a[r][c] = k <= i ? A[i * lda + k] : 0.0;
+      x[r][c] = i == k ? 1.0 : 0.0;
     }
   }
   if (tk == 0) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ct[0][i0 + r] = a[r][0];
+    for (int r = 0; r < 4; ++r) ct[0][ti + 16 * r] = a[r][0];
   }
-  if (ti == 0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) xr[0][k0 + c] = x[0][c];
-  }
-  if (tid == 0) ev[1] = a[1][1];
+  if (ti == 0) xr[0][tk] = x[0][0];
+  if (ti == 1 && tk == 1) ev[1] = a[0][0];
   __syncthreads();
   double d = ct[0][0];
   if (!(d > 0.0)) {
@@ -95,59 +97,73 @@ __device__ __forceinline__ void chol64_tile(double* A, int64_t lda, double* X, i
   }
   if (tid == 0) dv[0] = d;
   double rd = 1.0 / d;
-  for (int jb = 0; jb < kT; jb += 4) {
+  // Step j = 16 q + jj; the next column and row are in sample cn, the next but one
+  // diagonal entry in sample e2 (4: past the end).
+  auto step = [&](auto qc, auto cnc, auto e2c, int jj) {
+    constexpr int q = decltype(qc)::value, cn = decltype(cnc)::value, e2 = decltype(e2c)::value;
+    const int sl = jj & 1, sn = sl ^ 1;
+    // All of the step's LDS reads first, unconditionally.
+    double crv[4], ccv[4], xk[4];
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int j = jb + jj, sl = jj & 1, sn = sl ^ 1;
-      const int jn = j + 1, cn = (jj + 1) & 3, c2 = (jj + 2) & 3;
-      // All of the step's LDS reads first, unconditionally (a select after
-      // the load keeps them out of branches).
-      const double2 cr0 = *reinterpret_cast<const double2*>(&ct[sl][i0]);
-      const double2 cr1 = *reinterpret_cast<const double2*>(&ct[sl][i0 + 2]);
-      const double2 cc0 = *reinterpret_cast<const double2*>(&ct[sl][k0]);
-      const double2 cc1 = *reinterpret_cast<const double2*>(&ct[sl][k0 + 2]);
-      const double2 xx0 = *reinterpret_cast<const double2*>(&xr[sl][k0]);
-      const double2 xx1 = *reinterpret_cast<const double2*>(&xr[sl][k0 + 2]);
-      const double cj = ct[sl][jn < kT ? jn : j];
-      const double en = ev[sn];
-      const double crv[4] = {cr0.x, cr0.y, cr1.x, cr1.y};
-      const double ccv[4] = {cc0.x, cc0.y, cc1.x, cc1.y};
-      double m[4], ck[4];
-      const double xk[4] = {xx0.x, xx0.y, xx1.x, xx1.y};
+    for (int r = q; r < 4; ++r) crv[r] = ct[sl][ti + 16 * r];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m[r] = crv[r] * (i0 + r > j ? rd : 0.0);   // (entries above j are finite)
+    for (int c = q; c < 4; ++c) ccv[c] = ct[sl][tk + 16 * c];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) ck[c] = k0 + c > j ? ccv[c] : 0.0;
-      if (jn < kT) {
-        if (tk == jn / 4) {
+    for (int c = 0; c <= q; ++c) xk[c] = xr[sl][tk + 16 * c];
+    const double cj = ct[sl][cn < 4 ? 16 * q + jj + 1 : 0];
+    const double en = ev[sn];
+    double m[4], ck[4];
+    m[q] = crv[q] * (ti > jj ? rd : 0.0);                  // (entries above j are finite)
+    ck[q] = tk > jj ? ccv[q] : 0.0;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) ct[sn][i0 + r] = a[r][cn] - m[r] * ck[cn];
-        }
-        if (ti == jn / 4) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) xr[sn][k0 + c] = x[cn][c] - m[cn] * xk[c];
-        }
-        if (jn + 1 < kT && ti == (jn + 1) / 4 && tk == (jn + 1) / 4) ev[sl] = a[c2][c2] - m[c2] * ck[c2];
-        // next pivot: entry (j + 1, j + 1) after this step's update
-        double dn = en - (cj * rd) * cj;
-        if (!(dn > 0.0)) {
-          if (tid == 0) info[0] = 1;
-          dn = 1.0;
-        }
-        if (tid == 0) dv[jn] = dn;
-        rd = 1.0 / dn;
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          a[r][c] -= m[r] * ck[c];
-          x[r][c] -= m[r] * xk[c];
-        }
-      }
-      __syncthreads();
+    for (int r = q + 1; r < 4; ++r) {
+      m[r] = crv[r] * rd;
+      ck[r] = ccv[r];
     }
-  }
+    if constexpr (cn < 4) {
+      const int tn = (jj + 1) % 16;
+      if (tk == tn) {
+#pragma unroll
+        for (int r = cn; r < 4; ++r) ct[sn][ti + 16 * r] = a[r][cn] - m[r] * ck[cn];
+      }
+      if (ti == tn) {
+#pragma unroll
+        for (int c = 0; c <= cn; ++c) xr[sn][tk + 16 * c] = c <= q ? x[cn][c] - m[cn] * xk[c <= q ? c : q] : x[cn][c];
+      }
+      if constexpr (e2 < 4) {
+        const int t2 = (jj + 2) % 16;
+        if (ti == t2 && tk == t2) ev[sl] = a[e2][e2] - m[e2] * ck[e2];
+      }
+      // next pivot: entry (j + 1, j + 1) after this step's update
+      double dn = en - (cj * rd) * cj;
+      if (!(dn > 0.0)) {
+        if (tid == 0) info[0] = 1;
+        dn = 1.0;
+      }
+      if (tid == 0) dv[16 * q + jj + 1] = dn;
+      rd = 1.0 / dn;
+    }
+#pragma unroll
+    for (int r = q; r < 4; ++r) {
+#pragma unroll
+      for (int c = q; c <= r; ++c) a[r][c] -= m[r] * ck[c];
+#pragma unroll
+      for (int c = 0; c <= q; ++c) x[r][c] -= m[r] * xk[c];
+    }
+    __syncthreads();
+  };
+  auto phase = [&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    using Next = std::integral_constant<int, q + 1>;
+#pragma unroll 1
+    for (int jj = 0; jj < 14; ++jj) step(qc, qc, qc, jj);
+    step(qc, qc, Next{}, 14);
+    step(qc, Next{}, Next{}, 15);
+  };
+  phase(std::integral_constant<int, 0>{});
+  phase(std::integral_constant<int, 1>{});
+  phase(std::integral_constant<int, 2>{});
+  phase(std::integral_constant<int, 3>{});
   double* sq = ct[0];   // square roots of the pivots (the ring is free now)
   if (tid < kT) sq[tid] = sqrt(dv[tid]);
   __syncthreads();
@@ -155,7 +171,7 @@ __device__ __forceinline__ void chol64_tile(double* A, int64_t lda, double* X, i
   for (int r = 0; r < 4; ++r) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int i = i0 + r, k = k0 + c;
+      const int i = ti + 16 * r, k = tk + 16 * c;
       A[i * lda + k] = k < i ? a[r][c] / sq[k] : (k == i ? sq[i] : 0.0);
       X[i * ldx + k] = k <= i ? x[r][c] / sq[i] : 0.0;
     }
