@@ -219,7 +219,7 @@ sdq_status sdq_quantize_check(const void* workspace_dev, void* stream);
  *                            correction of the jointly quantized block.
  * u_dev: fp64 [k x k] upper factor as from sdq_hessian_factor.  workspace:
  * sdq_quantize_compensated_workspace_bytes (the plain encoder's plus about
- * 8 n (k + 2B + M) + 24 nb B^2 bytes).  Codes and scales as sdq_quantize; the
+ * 8 n (k + 2B) + 24 nb B^2 bytes).  Codes and scales as sdq_quantize; the
  * non-finite flag is reported by sdq_quantize_check on the same workspace.
  * Errors as sdq_quantize, and SDQ_ERR_ARG for an unknown update.
  */
@@ -342,7 +342,7 @@ sdq_status sdq_linear_group_expanded(int64_t m, int32_t count, const void* const
  *    return SDQ_ERR_WORKSPACE; they fit for every one-to-sixteen-row call on
  *    2-bit fields up to k = 28672 at OSR 8, and prefill while
  *    m * k_up * 2 bytes (twice that without Had) plus 8 m bytes of row
- *    factors stay within the limit.
+ *    factors stay within the limit (digit planes where they fit).
  *  - The coefficient tables are not built here: call sdq_prepare_layout for
  *    the layout on the current device first, else SDQ_ERR_UNSUPPORTED.
  *  - All calls on one GPU share its array; nothing in it needs to start at
@@ -369,7 +369,8 @@ sdq_status sdq_expand_activations(const void* x_dev, sdq_dtype xt, int64_t m,
  * layout with the same k, block, m_up, levels and packing).  m = 1 (binary,
  * base-3 or k_up < 16384): addition-only lookup-table GEMV; 2 <= m <= 16 and
  * one row of ternary 2-bit fields with k_up >= 16384: exact int8 matrix-core
- * contraction against the fixed-point expansion; larger m: fp16 MFMA GEMM.
+ * contraction against the fixed-point expansion; larger m: matrix-core GEMM
+ * (give it the workspace size that the expansion was given).
  * accumulate as in sdq_linear.  Errors as sdq_linear. */
 sdq_status sdq_linear_expanded(int64_t m, const void* codes_dev, const float* scales_dev,
                                const sdq_layout* layout, float* y_dev, int32_t accumulate,

@@ -1,4 +1,6 @@
-// Prefill path of sdq_linear (m > 16 activation rows), the contraction:
+// Prefill path of sdq_linear (m > 16 activation rows), the contraction on fp16
+// x_tilde: layouts without Had, and workspaces that do not hold the digit planes
+// (prefill_digits.hip, which serves the rest):
 //
 //   gemm     y[i, r] = s_r * sum_j x_tilde[i, j] C[r, j]: the codes are expanded
 //            in registers to fp16 +1 / 0 / -1 and fed to the fp16 matrix cores

@@ -92,11 +92,11 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 // K steps of its split.  The step's x_tilde tile and its codes (four panels, 64
 // rows x 16 bytes each) come straight from global memory to a ring of D LDS
 // buffers, D - 1 steps ahead; one plain barrier per step with a counted wait, so
-// that the copies of the following steps stay in flight.  The codes go through
-// LDS because loads to registers between copies to LDS are served one kind after
-// the other: with the codes loaded to registers in each step, a workgroup paid
-// about one memory latency per step (a 64 x 256 tile, 15 steps: 38 us, against 8
-// without the code loads and 9 without the copies).
+// that the copies of the following steps stay in flight.  Codes loaded to
+// registers between the copies to LDS held up a workgroup's start (a 64 x 256
+// tile stopped after its first eight steps: 38 us, against 8 without the code
+// loads, 9 without the copies and 17 with both through LDS) and took the
+// registers of four steps; whole calls differ by a few per cent.
 template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
