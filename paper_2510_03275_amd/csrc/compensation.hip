@@ -37,6 +37,7 @@ namespace {
 
 constexpr int kT = 64;     // factorisation panel / GEMM tile
 constexpr int kTK = 16;    // GEMM k step
+constexpr int kER = 32;    // rows of a block error tile
 constexpr int kStage = kT * kTK / 256;   // operand elements staged per thread and k step
 // Triangular operands of a GEMM: their zeros are left out of the K range.
 constexpr int kTriB = 1;   // B[p][j] = 0 for p < j
@@ -346,8 +347,8 @@ __global__ __launch_bounds__(256) void gemm64_kernel(
 // weights: E = W_b - (s C_b) Eb^T with C_b the packed codes of samples j0 .. j0 + M - 1
 // (M a multiple of 32, j0 too: a 16-deep slice is one ternary word or half a
 // binary one) and Eb the B x M table; out[r][t] = E[r][t] / u[t][t] (kDiv) or
-// E[r][t].  64 x 64 tile, the loop of gemm64_kernel: the codes are decoded into
-// the LDS slice, so the scaled codes, the copy of the block and the division
+// E[r][t].  32 x 64 tile (each wave 16 x 32): the codes are decoded into the LDS
+// slice, so the scaled codes, the copy of the block and the division
 // take no pass of their own (61 us of passes and product per block of 4096 rows
 // and 512 samples before, 33 so; 16 us at the matrix cores' 77 TFLOP/s, but one
 // workgroup per CU shows the latency of its loads, here two slices ahead).
@@ -356,17 +357,17 @@ __global__ __launch_bounds__(256) void block_error_kernel(
     const uint32_t* __restrict__ codes, const float* __restrict__ scales, int64_t n, int64_t n_chunks, int64_t j0s,
     int64_t M, const double* __restrict__ e64, const double* __restrict__ w, int64_t ldw, int B,
     const double* __restrict__ u, int64_t ldu, double* __restrict__ out) {
-  __shared__ double As[2][kTK][kT + 2];
+  __shared__ double As[2][kTK][kER + 2];
   __shared__ double Bs[2][kTK][kT + 2];
   const int tid = threadIdx.x;
   const int lane = tid % 64, wave = tid / 64;
   const int wr = wave / 2, wc = wave % 2;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kT;
+  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kER;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kT;
-  // Codes: thread t decodes samples 4 (t % 4) .. + 3 of row t / 4; the table:
+  // Codes: thread t decodes samples 2 (t % 8) and the next of row t / 8; the table:
   // sample t % 16 of rows t / 16 + 16 q.  Rows past n have codes of 0 (padding) or
   // are not stored.
-  const int64_t row = min<int64_t>(i0 + tid / 4, n - 1);
+  const int64_t row = min<int64_t>(i0 + tid / 8, n - 1);
   const double s = static_cast<double>(scales[row]);
   const uint32_t* crow = codes + ((row / kPanel) * n_chunks * kPanel + row % kPanel) * 4;
   const double* eb = e64 + (t0 + tid / 16) * M + tid % 16;
@@ -382,32 +383,28 @@ __global__ __launch_bounds__(256) void block_error_kernel(
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t f = (word[buf] >> (BITS * (4 * (tid % 4) + q))) & ((1u << BITS) - 1u);
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t f = (word[buf] >> (BITS * (2 * (tid % 8) + q))) & ((1u << BITS) - 1u);
       const double code = BITS == 1 ? (f ? 1.0 : -1.0) : (f == 1u ? 1.0 : (f == 3u ? -1.0 : 0.0));
-      As[buf][4 * (tid % 4) + q][tid / 4] = s * code;
-      Bs[buf][tid % 16][tid / 16 + 16 * q] = rb[buf][q];
+      As[buf][2 * (tid % 8) + q][tid / 8] = s * code;
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Bs[buf][tid % 16][tid / 16 + 16 * q] = rb[buf][q];
   };
-  double4_t acc[2][2];
+  double4_t acc[2];
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) acc[r][c] = double4_t{0.0, 0.0, 0.0, 0.0};
+  for (int c = 0; c < 2; ++c) acc[c] = double4_t{0.0, 0.0, 0.0, 0.0};
   const int lr = lane % 16, lk = lane / 16;
   auto slice = [&](int cur, int64_t p0) {
     load(cur, p0 + 2 * kTK);
 #pragma unroll
     for (int kk = 0; kk < kTK / 4; ++kk) {
-      double a[2], b[2];
-#pragma unroll
-      for (int r = 0; r < 2; ++r) a[r] = As[cur][4 * kk + lk][32 * wr + 16 * r + lr];
+      double b[2];
+      const double a = As[cur][4 * kk + lk][16 * wr + lr];
 #pragma unroll
       for (int c = 0; c < 2; ++c) b[c] = Bs[cur][4 * kk + lk][32 * wc + 16 * c + lr];
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[c], acc[r][c], 0, 0, 0);
+      for (int c = 0; c < 2; ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c], acc[c], 0, 0, 0);
     }
     store(cur ^ 1);
     __syncthreads();
@@ -421,20 +418,18 @@ __global__ __launch_bounds__(256) void block_error_kernel(
     slice(1, p0 + kTK);
   }
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int c = 0; c < 2; ++c) {
+    const int64_t t = t0 + 32 * wc + 16 * c + lr;
+    const double piv = u ? u[t * ldu + t] : 1.0;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int64_t t = t0 + 32 * wc + 16 * c + lr;
-      const double piv = u ? u[t * ldu + t] : 1.0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t gi = i0 + 32 * wr + 16 * r + lk + 4 * v;
-        if (gi < n) {
-          const double e = w[gi * ldw + t] - acc[r][c][v];
-          out[gi * B + t] = u ? e / piv : e;
-        }
+    for (int v = 0; v < 4; ++v) {
+      const int64_t gi = i0 + 16 * wr + lk + 4 * v;
+      if (gi < n) {
+        const double e = w[gi * ldw + t] - acc[c][v];
+        out[gi * B + t] = u ? e / piv : e;
       }
     }
+  }
 }
 
 // Inverse X = L^-1 of lower-triangular 64 x 64 diagonal blocks, one per
@@ -728,7 +723,7 @@ sdq_status launch_quantize_compensated(const float* w, const sdq_layout* L, cons
     // E_b = W_b - (s C_b) E^T, and G = E_b diag(U_bb)^-1 or (joint) G = E_b V_b
     double* err = joint ? cw.ebuf : cw.gbuf;
     const double* piv = joint ? nullptr : u + b * B * k + b * B;
-    const dim3 egrid(static_cast<unsigned>(B / kT), static_cast<unsigned>((n + kT - 1) / kT));
+    const dim3 egrid(static_cast<unsigned>(B / kT), static_cast<unsigned>((n + kER - 1) / kER));
     if (F->bits == 1)
       block_error_kernel<1><<<egrid, 256, 0, stream>>>(static_cast<const uint32_t*>(fcodes), scales, n, F->n_chunks,
                                                        b * M, M, T->e64, cw.w64 + b * B, k, static_cast<int>(B),
