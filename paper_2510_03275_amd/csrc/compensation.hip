@@ -346,12 +346,13 @@ __global__ __launch_bounds__(256) void gemm64_kernel(
 // The block error of the compensated encoder straight from the codes and the
 // weights: E = W_b - (s C_b) Eb^T with C_b the packed codes of samples j0 .. j0 + M - 1
 // (M a multiple of 32, j0 too: a 16-deep slice is one ternary word or half a
-// binary one) and Eb the B x M table; out[r][t] = E[r][t] / u[t][t] (kDiv) or
-// E[r][t].  32 x 64 tile (each wave 16 x 32): the codes are decoded into the LDS
-// slice, so the scaled codes, the copy of the block and the division
-// take no pass of their own (61 us of passes and product per block of 4096 rows
-// and 512 samples before, 33 so; 16 us at the matrix cores' 77 TFLOP/s, but one
-// workgroup per CU shows the latency of its loads, here two slices ahead).
+// binary one) and Eb the B x M table; out[r][t] = E[r][t] / u[t][t], or
+// E[r][t] where u is null.  The codes are decoded into the LDS slice, so the scaled
+// codes, the copy of the block and the division take no pass of their own.  32 x 64
+// tile (each wave 16 x 32), so that 4096 rows and 256 columns give two workgroups
+// per CU and one multiplies while the other waits for its loads, issued two slices
+// ahead.  A block of 4096 rows and 512 samples: 61 us of passes and product before,
+// 33 with 64 x 64 tiles, 30 so; 16 us at the matrix cores' 77 TFLOP/s.
 template <int BITS>
 __global__ __launch_bounds__(256) void block_error_kernel(
     const uint32_t* __restrict__ codes, const float* __restrict__ scales, int64_t n, int64_t n_chunks, int64_t j0s,
@@ -642,9 +643,8 @@ sdq_status launch_hessian_factor(const double* h, int64_t k, double lam, double*
 
 // Workspace of the compensated encoder: the plain encoder's, then (256-byte
 // aligned) scratch row maxima, W64 (n x k), E and G (n x B each), and per block
-// the reversed diagonal
-// block of U, its inverse, the inverse reversed back (nb x B x B each) and
-// the triangular-inverse scratch (nb x 64 x B).
+// the reversed diagonal block of U, its inverse, the inverse reversed back
+// (nb x B x B each) and the triangular-inverse scratch (nb x 64 x B).
 struct CompWs {
   QuantWs q;
   uint32_t* rmax_scratch;

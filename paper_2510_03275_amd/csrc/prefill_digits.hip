@@ -21,7 +21,8 @@
 // accumulator v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A K
 // step is 64 samples.  The digit planes are stored as operand images: per step
 // and 32-row group three planes of 64 lanes x 16 bytes, then 64 lanes x 8
-// bytes, then the 64 block scales, so a tile is copied to LDS as one run and read without conflicts.
+// bytes, then the 64 block scales, so a tile is copied to LDS as one run and read
+// without conflicts.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
