@@ -245,21 +245,22 @@ sdq_status sdq_quantize_compensated(const float* w_dev, const sdq_layout* layout
  *                 base-3 codes in the order of their digits: per group of
  *                 four 80-code chunks, five 64-code steps), then the fp32
  *                 plane scale of every (row, block);
- *   m > 16:       x_tilde as three FP6 digit planes with a power-of-two scale
- *                 per 32 samples (m rounded up to 32 rows, k_up to 128
- *                 samples, 73 bytes per 32 samples), the row factors below,
- *                 and the partial sums of a contraction split over K; or,
- *                 for layouts with SDQ_HAD_NONE, an fp16 pair hi + lo of
- *                 m x k_up (rounded up to whole chunks) each, every row scaled
- *                 by a power of two p_i that keeps it inside fp16's normal
- *                 range, then p_i and 1 / p_i (fp32 [m] each);
- * for a base-3 layout and m > 16 the chunks are those of 2-bit fields, and the
- * 2-bit copy of the codes follows x_tilde (n_pad x ceil(k_up / 64) x 16 bytes).
+ *   m > 16:       powers of two p_i and 1 / p_i of the rows (fp32 [m] each),
+ *                 then x_tilde as three FP6 digit planes with a power-of-two
+ *                 scale per 32 samples (m rounded up to 32 rows, k_up to 128
+ *                 samples, 73 bytes per 32 samples) and the partial sums of a
+ *                 contraction split over K; or, for layouts with SDQ_HAD_NONE,
+ *                 an fp16 pair hi + lo of m x k_up (rounded up to whole chunks)
+ *                 each, every row scaled by p_i, which keeps it inside fp16's
+ *                 normal range;
+ * for a base-3 layout and m > 16 the chunks are those of 2-bit fields, the digit
+ * planes lie behind the place of one fp16 x_tilde, and the 2-bit copy of the codes
+ * (n_pad x ceil(k_up / 64) x 16 bytes) follows.
  * Calls with m > 16 also accept less: from the size of one fp16 x_tilde with its
  * row factors (and the 2-bit copy) on, a call takes the fastest form that fits
  * (fewer splits, then fp16 x_tilde; results differ within the stated accuracy).
- * An expansion and the contractions that read it must be given the same
- * workspace size. */
+ * An expansion and the contractions that read it may be given different sizes: the
+ * workspace tells which form it holds. */
 size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
 
 /*
@@ -267,7 +268,10 @@ size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
  * the decimated, Hadamard-restored reconstruction of the codes).  Computed as
  * x_tilde = per-block (x_b Had) D^T (D: Resample back to B), then
  * y[i, r] = s_r * sum_j C[r, j] x_tilde[i, j].  Equivalent to
- * sdq_expand_activations followed by sdq_linear_expanded on the same workspace.
+ * sdq_expand_activations followed by sdq_linear_expanded on the same workspace
+ * (within the accuracy below: for base-3 codes and m > 16 the separate expansion
+ * writes fp16 x_tilde, this call digit planes where they fit), and
+ * sdq_linear_expanded may follow it for other linears of the same input.
  *   x_dev        [m x k] activations of type xt (F16, BF16 or F32), row-major.
  *   m            activation rows, >= 0 (m = 0 is a no-op).  m = 1 with
  *                binary or base-3 codes or k_up < 16384: fp32 expansion and
@@ -365,12 +369,14 @@ sdq_status sdq_expand_activations(const void* x_dev, sdq_dtype xt, int64_t m,
                                   size_t workspace_bytes, void* stream);
 
 /* Second step of sdq_linear: y[i, r] = s_r * sum_j C[r, j] x_tilde[i, j] from
- * the x_tilde that sdq_expand_activations left in the workspace (same m and a
- * layout with the same k, block, m_up, levels and packing).  m = 1 (binary,
+ * the x_tilde that sdq_expand_activations (or sdq_linear, sdq_linear_group) left in
+ * the workspace (same m and a layout with the same k, block, m_up, levels and
+ * packing).  With m > 16 it also writes to the workspace, behind the expansion
+ * (partial sums; unpacked base-3 codes), so contractions that share one must be
+ * ordered like all calls that share a workspace.  m = 1 (binary,
  * base-3 or k_up < 16384): addition-only lookup-table GEMV; 2 <= m <= 16 and
  * one row of ternary 2-bit fields with k_up >= 16384: exact int8 matrix-core
- * contraction against the fixed-point expansion; larger m: matrix-core GEMM
- * (give it the workspace size that the expansion was given).
+ * contraction against the fixed-point expansion; larger m: matrix-core GEMM.
  * accumulate as in sdq_linear.  Errors as sdq_linear. */
 sdq_status sdq_linear_expanded(int64_t m, const void* codes_dev, const float* scales_dev,
                                const sdq_layout* layout, float* y_dev, int32_t accumulate,

@@ -500,7 +500,9 @@ __device__ inline void unpack_all(const uint32_t (&by)[4], const uint32_t* pat, 
 // zero fields.
 __global__ __launch_bounds__(256) void unpack_base3_kernel(const uint4* __restrict__ b3, int64_t n,
                                                            int64_t nch2, int64_t nch3, int64_t quads,
-                                                           int64_t total, uint4* __restrict__ fields) {
+                                                           int64_t total, uint4* __restrict__ fields,
+                                                           float* form) {
+  if (form && blockIdx.x == 0 && threadIdx.x == 0) *form = fabsf(*form);
   // Byte -> its five codes as 2-bit fields: digit i of q is the integer part
   // of 3 r after i + 1 steps of r <- fraction part of 3 r, from r = q / 256.
   __shared__ uint32_t pat[256];
@@ -555,14 +557,15 @@ __global__ __launch_bounds__(256) void unpack_base3_kernel(const uint4* __restri
 
 }  // namespace
 
-sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t* fields, hipStream_t stream) {
+sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t* fields, float* form,
+                               hipStream_t stream) {
   const sdq_layout F = fields_view(L);
   const int64_t groups = std::max<int64_t>(L->n_chunks, (4 * F.n_chunks + 4) / 5);
   const int64_t quads = (groups + 3) / 4;
   const int64_t total = L->n_pad * quads;
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>((total + 255) / 256, 16384));
   unpack_base3_kernel<<<grid, 256, 0, stream>>>(static_cast<const uint4*>(codes), L->n, F.n_chunks, L->n_chunks,
-                                                quads, total, reinterpret_cast<uint4*>(fields));
+                                                quads, total, reinterpret_cast<uint4*>(fields), form);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "base-3 unpack launch");
   return SDQ_OK;

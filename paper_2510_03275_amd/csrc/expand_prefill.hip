@@ -95,6 +95,15 @@ constexpr int digit_sample(int j) {
   return LEVELS == 3 ? 16 * (j / 16) + 2 * (j % 8) + (j / 8) % 2 : 4 * (j % 8) + j / 8;
 }
 
+// The 32-block b32 of a row: its place, as store_digits writes it (tile of its K
+// step and row group, and the lane of the operand image).
+template <int LEVELS>
+__device__ inline int digit_slot(int64_t row, int64_t n_rg, int64_t b32, int64_t* tile) {
+  const int64_t step = LEVELS == 3 ? b32 / 2 : 2 * (b32 / 4) + b32 % 2;
+  *tile = step * n_rg + row / 32;
+  return static_cast<int>(row % 32) + 32 * static_cast<int>(LEVELS == 3 ? b32 % 2 : (b32 / 2) % 2);
+}
+
 // One lane: the 32 samples of one row's block, A[v] = sample 8 (v / 4) + v % 4
 // and Bv[v] = sample 8 (v / 4) + 4 + v % 4, to the digit planes of 32-block kb
 // of row `row` (kb in samples / 32 over the row).  zero_to: the 32-blocks kb +
@@ -126,14 +135,8 @@ __device__ inline void store_digits(const floatx16& A, const floatx16& Bv, int64
   const u32x6 q[3] = {cvt_fp6(p0[0], p0[1], 1.0f), cvt_fp6(p1[0], p1[1], 0.03125f),
                       cvt_fp6(p2[0], p2[1], 0.0009765625f)};
   if (row / 32 >= n_rg) return;
-  const int r32 = static_cast<int>(row % 32);
-  auto slot = [&](int64_t b32, int64_t* tile) {     // 32-block b32 of the row: its step and K half
-    const int64_t step = LEVELS == 3 ? b32 / 2 : 2 * (b32 / 4) + b32 % 2;
-    *tile = step * n_rg + row / 32;
-    return r32 + 32 * static_cast<int>(LEVELS == 3 ? b32 % 2 : (b32 / 2) % 2);
-  };
   int64_t t;
-  const int ln = slot(kb, &t);
+  const int ln = digit_slot<LEVELS>(row, n_rg, kb, &t);
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     uint8_t* dst = planes + t * kDigitTile + p * kDigitPlane;
@@ -142,7 +145,7 @@ __device__ inline void store_digits(const floatx16& A, const floatx16& Bv, int64
   }
   planes[t * kDigitTile + 3 * kDigitPlane + ln] = static_cast<uint8_t>(mb >= 0x7F800000u ? 255u : eb);
   for (int64_t z = kb + 1; z < zero_to; ++z) {
-    const int lz = slot(z, &t);
+    const int lz = digit_slot<LEVELS>(row, n_rg, z, &t);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       uint8_t* dst = planes + t * kDigitTile + p * kDigitPlane;
@@ -150,6 +153,71 @@ __device__ inline void store_digits(const floatx16& A, const floatx16& Bv, int64
       *reinterpret_cast<uint2*>(dst + 1024 + 8 * lz) = make_uint2(0u, 0u);
     }
     planes[t * kDigitTile + 3 * kDigitPlane + lz] = 0;
+  }
+}
+
+// fp16 x_tilde (rows of k_up_pad samples) and its row factors from the digit planes
+// of ternary codes, one row per workgroup: for contractions of base-3 codes called
+// apart, whose unpacked codes need the place behind fp16 x_tilde, after a whole call
+// that left digit planes.  Nothing where fp16 x_tilde is there already (1.5 us).
+// p_i = 2^(12 - E) with E the row's largest block exponent: samples below 2^14.  The
+// form word stays negative, since workgroups still to start read it; the unpacking
+// that follows makes it positive.
+__global__ __launch_bounds__(256) void digits_to_half_kernel(DigitPlanes dp, int64_t m, int64_t k_up_pad,
+                                                             _Float16* __restrict__ xt) {
+  if (!(dp.row_fac[m] < 0.0f)) return;
+  __shared__ int wmax[4];
+  const int64_t row = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int64_t blocks = k_up_pad / 32;
+  int e = 0;                                       // the row's largest exponent of a finite block
+  for (int64_t b = tid; b < blocks; b += 256) {
+    int64_t t;
+    const int ln = digit_slot<3>(row, dp.n_rg, b, &t);
+    const int s = dp.planes[t * kDigitTile + 3 * kDigitPlane + ln];
+    if (s < 255) e = max(e, s);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off /= 2) e = max(e, __shfl_xor(e, off, 64));
+  if (tid % 64 == 0) wmax[tid / 64] = e;
+  __syncthreads();
+  e = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])) - 127;
+  const int pe = min(max(12 - e, -126), 126);
+  if (tid == 0) {
+    dp.row_fac[row] = ldexpf(1.0f, pe);
+    dp.row_fac[m + row] = row == 0 ? -ldexpf(1.0f, -pe) : ldexpf(1.0f, -pe);
+  }
+  for (int64_t b = tid; b < blocks; b += 256) {
+    int64_t t;
+    const int ln = digit_slot<3>(row, dp.n_rg, b, &t);
+    const uint8_t* base = dp.planes + t * kDigitTile;
+    const int s = base[3 * kDigitPlane + ln];
+    uint32_t w[3][6];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint4 lo = *reinterpret_cast<const uint4*>(base + p * kDigitPlane + 16 * ln);
+      const uint2 hi = *reinterpret_cast<const uint2*>(base + p * kDigitPlane + 1024 + 8 * ln);
+      w[p][0] = lo.x; w[p][1] = lo.y; w[p][2] = lo.z; w[p][3] = lo.w; w[p][4] = hi.x; w[p][5] = hi.y;
+    }
+    const float scale = s == 255 ? __uint_as_float(0x7FC00000u) : ldexpf(1.0f, s - 127 + pe - 13);
+    half8 out[4];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {                 // K slot j
+      int v = 0;                                   // in units of 2^-13: planes of 1 / 8, weights 1, 2^-5, 2^-10
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const int at = 6 * j, q = at / 32, sh = at % 32;
+        uint32_t f = w[p][q] >> sh;
+        if (sh > 26) f |= w[p][q + 1] << (32 - sh);
+        const int ex = (f >> 3) & 3, man = f & 7;  // e2m3, bias 1
+        const int mag = ex ? (8 + man) << (ex - 1) : man;
+        v = 32 * v + ((f & 32u) ? -mag : mag);
+      }
+      const int smp = digit_sample<3>(j);
+      out[smp / 8][smp % 8] = static_cast<_Float16>(static_cast<float>(v) * scale);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<half8*>(xt + row * k_up_pad + 32 * b + 8 * q) = out[q];
   }
 }
 
@@ -170,12 +238,13 @@ __device__ inline void rows_to_lanes(floatx16& a, floatx16& b) {
 // max |x| over its k values (16-byte loads, 1 KB per wave load) and writes
 // p = 2^e and 1 / p with e = 14 - ceil2(a max(e1max, 1)), where ceil2(v) is
 // the exponent ex of v = f 2^ex, f in [0.5, 1) (so v < 2^ex).  A row of zeros
-// or with a non-finite maximum keeps p = 1.
+// or with a non-finite maximum keeps p = 1.  digits: 1 / p_0 is written negative
+// (the form word of digit planes).
 template <sdq_dtype XT>
 __global__ __launch_bounds__(256) void prefill_row_scale_kernel(const void* __restrict__ x, int64_t m,
                                                                 int64_t k, float e1, float* __restrict__ fac,
                                                                 _Float16* __restrict__ pad_out, int64_t k_up,
-                                                                int64_t k_up_pad) {
+                                                                int64_t k_up_pad, bool digits) {
   const int lane = threadIdx.x % 64;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + threadIdx.x / 64;
   if (i >= m) return;
@@ -214,7 +283,7 @@ __global__ __launch_bounds__(256) void prefill_row_scale_kernel(const void* __re
       e = min(max(14 - ex, -126), 126);
     }
     fac[i] = ldexpf(1.0f, e);
-    fac[m + i] = ldexpf(1.0f, -e);
+    fac[m + i] = digits && i == 0 ? -ldexpf(1.0f, -e) : ldexpf(1.0f, -e);
   }
 }
 
@@ -386,7 +455,7 @@ __global__ __launch_bounds__(256) void expand_prefill_tiled_kernel(
   if constexpr (OUT != 0) {
     static_assert(RT == 2, "two 32-row tiles per wave");
     const int64_t row = i0 + 64 * wr + lane;
-    const float pinv = fac[m + min<int64_t>(row, m - 1)];
+    const float pinv = fabsf(fac[m + min<int64_t>(row, m - 1)]);   // (the form word is negative)
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
       const int c = c0 + 64 * wc + 32 * ct;
@@ -482,6 +551,7 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
   const int s = jx % n_ss;
   const int64_t g = static_cast<int64_t>(jx / n_ss) * kXcds + xcd;
   const int64_t it_begin = g * ipg, it_end = min<int64_t>(n_items, it_begin + ipg);
+  if (OUT != 0 && id == 0 && tid == 0) dp.row_fac[m] = -1.0f;   // the form word: digit planes
   if (it_begin >= it_end) return;
   // E^T fragments of this lane's sample, k = 16 ks + 8 (lane / 32) .. + 7.
   const int col = 128 * s + 32 * wave + lane % 32;
@@ -625,17 +695,26 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
 // hi + lo and run the GEMM on both.
 bool prefill_split(const sdq_layout* L) { return L->hadamard == SDQ_HAD_NONE; }
 
+sdq_status launch_digits_to_half(int64_t m, const sdq_layout* L, void* ws, size_t at, hipStream_t stream) {
+  digits_to_half_kernel<<<dim3(static_cast<unsigned>(m)), dim3(256), 0, stream>>>(
+      digit_planes(L, m, ws, at), m, L->n_chunks * L->codes_per_chunk,
+      reinterpret_cast<_Float16*>(static_cast<char*>(ws) + prefill_fac_bytes(m)));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_error(e, "digit planes to fp16 launch");
+  return SDQ_OK;
+}
+
 sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                                 const Tables* T, void* ws, bool digits, hipStream_t stream) {
+                                 const Tables* T, void* ws, size_t digits_at, hipStream_t stream) {
   const int64_t k_up_pad = L->n_chunks * L->codes_per_chunk;
-  const DigitPlanes dp = digits ? digit_planes(L, m, ws) : DigitPlanes{};
-  _Float16* xbuf = static_cast<_Float16*>(ws);
+  const bool digits = digits_at != 0;
+  const DigitPlanes dp = digits ? digit_planes(L, m, ws, digits_at) : DigitPlanes{};
+  float* fac = static_cast<float*>(ws);
+  char* planes = static_cast<char*>(ws) + prefill_fac_bytes(m);
+  _Float16* xbuf = reinterpret_cast<_Float16*>(planes);
   _Float16* xlo = !digits && prefill_split(L)
-                      ? reinterpret_cast<_Float16*>(static_cast<char*>(ws) +
-                                                    align_up(static_cast<size_t>(m) * k_up_pad * 2, 256))
+                      ? reinterpret_cast<_Float16*>(planes + align_up(static_cast<size_t>(m) * k_up_pad * 2, 256))
                       : nullptr;
-  float* fac = digits ? dp.row_fac
-                      : reinterpret_cast<float*>(static_cast<char*>(ws) + prefill_planes_bytes(L, m));
   // fp16 / bf16 activations, B = 128 or 256, no fp16 pair: the E-stationary
   // kernel.  Workgroups: one per compute unit, spread over the 128-sample
   // slices of M; each walks an even share of the (row tile, block) items.
@@ -648,7 +727,7 @@ sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const s
     const dim3 sgrid(static_cast<unsigned>((m + 3) / 4));
     auto scale = [&](auto t) {
       prefill_row_scale_kernel<decltype(t)::value>
-          <<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad);
+          <<<sgrid, dim3(256), 0, stream>>>(x, m, L->k, T->e1max, fac, pad_out, L->k_up, k_up_pad, digits);
     };
     if (xt == SDQ_F32) scale(std::integral_constant<sdq_dtype, SDQ_F32>{});
     else if (xt == SDQ_BF16) scale(std::integral_constant<sdq_dtype, SDQ_BF16>{});

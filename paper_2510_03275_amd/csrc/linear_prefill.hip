@@ -144,7 +144,8 @@ template <int LEVELS, int NC, int W>
 __global__ __launch_bounds__(64 * W, 1) void gemm_prefill_kernel(
     const _Float16* __restrict__ xt, const float* __restrict__ row_inv, LinearSet S, int64_t m,
     int64_t n_chunks, int64_t k_up_pad, int64_t m_tiles, int64_t n_tiles, int64_t t_base, int64_t t_count,
-    int accumulate) {
+    int accumulate, const float* form) {
+  if (form && *form < 0.0f) return;           // a contraction called apart: digit planes are there
   __shared__ __attribute__((aligned(1024))) _Float16 As[kABufs][kTileHalves];
   constexpr int RPW = kBM / (W / 4);          // activation rows per wave
   constexpr int RT = RPW / 32;                 // 32-row MFMA tiles per wave
@@ -292,24 +293,21 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_prefill_kernel(
 
 }  // namespace
 
-size_t prefill_planes_bytes(const sdq_layout* L, int64_t m) {
-  const int64_t k_up_pad = L->n_chunks * L->codes_per_chunk;
-  return align_up(static_cast<size_t>(m) * k_up_pad * 2, 256) * (prefill_split(L) ? 2 : 1);
-}
-
 size_t prefill_ws_bytes(const sdq_layout* L, int64_t m) {
-  return prefill_planes_bytes(L, m) + align_up(static_cast<size_t>(m) * 2 * sizeof(float), 256);
+  const int64_t k_up_pad = L->n_chunks * L->codes_per_chunk;
+  return prefill_fac_bytes(m) + align_up(static_cast<size_t>(m) * k_up_pad * 2, 256) * (prefill_split(L) ? 2 : 1);
 }
 
 sdq_status launch_prefill_contract(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
-                                   hipStream_t stream) {
+                                   bool by_form, hipStream_t stream) {
   S.first[0] = 0;
   for (int j = 0; j < S.count; ++j) S.first[j + 1] = S.first[j] + (S.n[j] + kBN - 1) / kBN;
   for (int j = S.count + 1; j <= kMaxGroup; ++j) S.first[j] = S.first[S.count];
   const int64_t n_tiles = S.first[S.count];
   const int64_t k_up_pad = L->n_chunks * L->codes_per_chunk;
   const size_t plane = align_up(static_cast<size_t>(m) * k_up_pad * 2, 256);
-  const float* row_inv = reinterpret_cast<const float*>(static_cast<const char*>(ws) + prefill_planes_bytes(L, m)) + m;
+  const float* row_inv = prefill_form(ws, m);      // 1 / p_i; its first word tells the form
+  const float* form = by_form ? row_inv : nullptr;
   // The kernel addresses x_tilde with 32-bit element offsets: launch row
   // chunks of at most 2^31 elements.
   const int64_t rows_max = std::max<int64_t>(kBM, ((int64_t{1} << 31) / k_up_pad) / kBM * kBM);
@@ -322,7 +320,8 @@ sdq_status launch_prefill_contract(int64_t m, LinearSet S, const sdq_layout* L, 
   static const char* env_w = std::getenv("SDQ_PF_WAVES");
   const int waves = env_w && std::atoi(env_w) == 4 ? 4 : 8;
   for (int pass = 0; pass < passes; ++pass) {
-    const _Float16* xbuf = reinterpret_cast<const _Float16*>(static_cast<const char*>(ws) + pass * plane);
+    const _Float16* xbuf = reinterpret_cast<const _Float16*>(static_cast<const char*>(ws) + prefill_fac_bytes(m) +
+                                                             pass * plane);
     const int acc = accumulate || pass > 0 ? 1 : 0;
     for (int64_t r0 = 0; r0 < m; r0 += rows_max) {
       const int64_t mm = std::min(rows_max, m - r0);
@@ -344,11 +343,11 @@ sdq_status launch_prefill_contract(int64_t m, LinearSet S, const sdq_layout* L, 
         if (waves == 8)
           gemm_prefill_kernel<LV, NC, 8><<<ggrid, dim3(512), 0, stream>>>(xc, row_inv + r0, Sc, mm, L->n_chunks,
                                                                         k_up_pad, m_tiles, n_tiles, t_base,
-                                                                        t_count, acc);
+                                                                        t_count, acc, form);
         else
           gemm_prefill_kernel<LV, NC, 4><<<ggrid, dim3(256), 0, stream>>>(xc, row_inv + r0, Sc, mm, L->n_chunks,
                                                                         k_up_pad, m_tiles, n_tiles, t_base,
-                                                                        t_count, acc);
+                                                                        t_count, acc, form);
       };
       using L2_ = std::integral_constant<int, 2>;
       using L3_ = std::integral_constant<int, 3>;

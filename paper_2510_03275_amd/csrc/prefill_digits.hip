@@ -101,7 +101,8 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
-    int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part) {
+    int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part, const float* form) {
+  if (form && !(*form < 0.0f)) return;             // a contraction called apart: fp16 x_tilde is there
   constexpr int RG = WM * RT;
   constexpr int W = WM * WN;
   constexpr int BN = 32 * CT * WN;                 // weight rows of the tile
@@ -298,7 +299,8 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
 // floats per thread and load (4 where y is 16-byte aligned).
 template <int V>
 __global__ __launch_bounds__(256) void reduce_digits_kernel(LinearSet S, DigitParts part, int64_t m, int splits,
-                                                            int accumulate) {
+                                                            int accumulate, const float* form) {
+  if (form && !(*form < 0.0f)) return;
   const int lin = blockIdx.y;
   const int64_t cnt = m * S.n[lin];
   const float* __restrict__ src = part.base + part.off[lin];
@@ -377,20 +379,13 @@ int64_t part_floats(const int64_t* n, int count, int64_t m) {
 
 }  // namespace
 
-DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws) {
+DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws, size_t at) {
   DigitPlanes d;
   d.n_rg = (m + 31) / 32;
   d.n_steps = 2 * ((L->k_up + 127) / 128);
-  char* base = static_cast<char*>(ws);
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    char* at = base + off;
-    off += align_up(bytes, 256);
-    return at;
-  };
-  d.planes = reinterpret_cast<uint8_t*>(take(static_cast<size_t>(d.n_steps) * d.n_rg * kDigitTile));
-  d.row_fac = reinterpret_cast<float*>(take(static_cast<size_t>(m) * 2 * sizeof(float)));
-  d.bytes = off;
+  d.row_fac = static_cast<float*>(ws);
+  d.planes = static_cast<uint8_t*>(ws) + at;
+  d.bytes = at + align_up(static_cast<size_t>(d.n_steps) * d.n_rg * kDigitTile, 256);
   return d;
 }
 
@@ -422,9 +417,10 @@ DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_
   return best;
 }
 
-sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
-                                 void* part_ws, size_t part_bytes, hipStream_t stream) {
-  const DigitPlanes d = digit_planes(L, m, ws);
+sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws, size_t at,
+                                 void* part_ws, size_t part_bytes, bool by_form, hipStream_t stream) {
+  const DigitPlanes d = digit_planes(L, m, ws, at);
+  const float* form = by_form ? prefill_form(ws, m) : nullptr;
   const DigitPlan plan = digit_plan(S.n, S.count, L->k_up, m, part_bytes);
   const DigitShape& shape = kShapes[plan.shape];
   S.first[0] = 0;
@@ -449,7 +445,7 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
     static_assert(kShapes[I].rg == WM * RT && kShapes[I].bn == 32 * WN * CT, "shape");                   \
     gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, D><<<grid, dim3(64 * WM * WN), 0, stream>>>(            \
         d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,              \
-        plan.steps_per, acc, part);                                                                      \
+        plan.steps_per, acc, part, form);                                                                \
     break
 #define SDQ_DIG_SHAPES(LV)                                                                               \
   switch (plan.shape) {                                                                                  \
@@ -474,8 +470,8 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
     const int v = al ? 4 : 1;
     const dim3 rgrid(static_cast<unsigned>(std::min<int64_t>((most + 256 * v - 1) / (256 * v), 4096)),
                      static_cast<unsigned>(S.count));
-    if (al) reduce_digits_kernel<4><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0);
-    else reduce_digits_kernel<1><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0);
+    if (al) reduce_digits_kernel<4><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0, form);
+    else reduce_digits_kernel<1><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0, form);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "digit-plane GEMM launch");

@@ -461,17 +461,33 @@ static bool needs_unpack(const sdq_layout* L, int64_t m) {
   return L->packing == SDQ_PACK_BASE3 && !(m <= 16 && decode_reads_base3(L, m));
 }
 
-static size_t path_ws_bytes(const sdq_layout* P, int64_t m, bool digits = false) {
-  return m <= 16 ? decode_ws_bytes(P, m) : (digits ? digit_planes(P, m, nullptr).bytes : prefill_ws_bytes(P, m));
+// The path's part of the workspace: the expansion.  at: prefill on digit planes
+// from that byte on (0: fp16 x_tilde).
+static size_t path_ws_bytes(const sdq_layout* P, int64_t m, size_t at = 0) {
+  return m <= 16 ? decode_ws_bytes(P, m) : (at ? digit_planes(P, m, nullptr, at).bytes : prefill_ws_bytes(P, m));
+}
+
+// Where digit planes lie: behind the row factors; for base-3 layouts behind fp16
+// x_tilde, into which a later contraction called apart turns them
+// (launch_digits_to_half) before it unpacks its codes behind it.  Workspaces that
+// no other call reads (`own`: sdq_linear_noalloc's) need no such place.
+static size_t digits_at(const sdq_layout* L, int64_t m, bool own) {
+  const sdq_layout F = fields_view(L);
+  return L->packing == SDQ_PACK_BASE3 && !own ? prefill_ws_bytes(&F, m) : prefill_fac_bytes(m);
+}
+
+// Whether prefill calls of a layout have the choice of digit planes.
+static bool digits_possible(const sdq_layout* L, int64_t m) {
+  return m > 16 && !prefill_split(L) && L->k_up <= kDigitMaxK;
 }
 
 // The least workspace of a linear call over linears of n[j] rows (layout
 // family L): the path's part (the expansion at offset 0), then for base-3
 // codes read as 2-bit fields each linear's unpacked copy.
-static size_t set_ws_bytes(const sdq_layout* L, const int64_t* n, int count, int64_t m, bool digits = false) {
-  if (!needs_unpack(L, m)) return path_ws_bytes(L, m, digits);
+static size_t set_ws_bytes(const sdq_layout* L, const int64_t* n, int count, int64_t m, size_t at = 0) {
+  if (!needs_unpack(L, m)) return path_ws_bytes(L, m, at);
   const sdq_layout F = fields_view(L);
-  size_t off = align_up(path_ws_bytes(&F, m, digits), 256);
+  size_t off = align_up(path_ws_bytes(&F, m, at), 256);
   for (int j = 0; j < count; ++j) {
     sdq_layout Lj = *L;
     Lj.n = n[j];
@@ -494,22 +510,22 @@ static size_t linear_ws_bytes(const sdq_layout* L, int64_t m) { return group_ws_
 // any workspace of group_ws_bytes and more and takes what fits.
 static size_t group_ws_wanted(const sdq_layout* Ls, int count, int64_t m) {
   const size_t least = group_ws_bytes(Ls, count, m);
-  if (m <= 16 || prefill_split(&Ls[0]) || Ls[0].k_up > kDigitMaxK) return least;
+  if (!digits_possible(&Ls[0], m)) return least;
   int64_t n[kMaxGroup] = {};
   for (int j = 0; j < count; ++j) n[j] = Ls[j].n;
-  const size_t own = align_up(set_ws_bytes(&Ls[0], n, count, m, true), 256);
+  const size_t own = align_up(set_ws_bytes(&Ls[0], n, count, m, digits_at(&Ls[0], m, false)), 256);
   return std::max(least, own + digit_plan(n, count, Ls[0].k_up, m, SIZE_MAX).part_bytes);
 }
 
-// Whether a prefill call runs on digit planes.  In one call (expansion and
-// contraction of the set S) if they and the unpacked codes fit.  An expansion
-// and a contraction called apart (S NULL) decide by what both know: the layout
-// family, m and the workspace size; base-3 layouts, whose unpacked codes depend on
-// the linears, then stay with fp16 x_tilde.
-static bool use_digits(const sdq_layout* L, int64_t m, const LinearSet* S, size_t ws_bytes) {
-  if (m <= 16 || prefill_split(L) || L->k_up > kDigitMaxK) return false;
-  if (S) return set_ws_bytes(L, S->n, S->count, m, true) <= ws_bytes;
-  return L->packing != SDQ_PACK_BASE3 && path_ws_bytes(L, m, true) <= ws_bytes;
+// The place of a prefill call's digit planes, or 0 for fp16 x_tilde.  One call
+// (expansion and contraction of the set S) takes them if they and the unpacked codes
+// fit, an expansion called apart (S NULL) if they fit; for base-3 layouts, whose
+// unpacked codes depend on the linears, it writes fp16 x_tilde.
+static size_t use_digits(const sdq_layout* L, int64_t m, const LinearSet* S, size_t ws_bytes, bool own = false) {
+  if (!digits_possible(L, m)) return 0;
+  const size_t at = digits_at(L, m, own);
+  if (S) return set_ws_bytes(L, S->n, S->count, m, at) <= ws_bytes ? at : 0;
+  return L->packing != SDQ_PACK_BASE3 && path_ws_bytes(L, m, at) <= ws_bytes ? at : 0;
 }
 
 size_t sdq_linear_workspace_bytes(const sdq_layout* L, int64_t m) {
@@ -540,7 +556,7 @@ static sdq_status linear_common(const sdq_layout* L, int64_t m, size_t ws_bytes,
 // The expansion for layout L; `zero`: the set whose outputs the decode
 // expansion zeroes for a split-K GEMV (or NULL).
 static sdq_status expand_impl(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                              void* ws, const LinearSet* zero, bool digits, void* stream,
+                              void* ws, const LinearSet* zero, size_t at, void* stream,
                               bool may_allocate = true) {
   if (xt != SDQ_F16 && xt != SDQ_BF16 && xt != SDQ_F32) return set_error(SDQ_ERR_ARG, "bad dtype");
   if (!x) return set_error(SDQ_ERR_ARG, "x is NULL");
@@ -552,14 +568,16 @@ static sdq_status expand_impl(const void* x, sdq_dtype xt, int64_t m, const sdq_
   if (st != SDQ_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   return m <= 16 ? launch_decode_expand(x, xt, m, P, T, ws, zero, s)
-                 : launch_prefill_expand(x, xt, m, P, T, ws, digits, s);
+                 : launch_prefill_expand(x, xt, m, P, T, ws, at, s);
 }
 
 // The contraction of every linear of S (layout family L) against the
 // expansion in ws; base-3 codes on the paths that read 2-bit fields are
-// unpacked first, each into its own part of the workspace.
+// unpacked first, each into its own part of the workspace.  at: the digit planes that
+// the same call's expansion wrote (0: fp16); apart: the expansion was another
+// call's, of whatever form.
 static sdq_status contract_impl(int64_t m, LinearSet S, const sdq_layout* L, bool accumulate, void* ws,
-                                size_t ws_bytes, bool digits, bool y_ready, void* stream) {
+                                size_t ws_bytes, size_t at, bool apart, void* stream) {
   for (int j = 0; j < S.count; ++j) {
     if (!S.codes[j] || !S.scales[j] || !S.y[j]) return set_error(SDQ_ERR_ARG, "NULL pointer argument");
     if (!aligned16(S.codes[j])) return set_error(SDQ_ERR_ARG, "codes are not 16-byte aligned");
@@ -569,25 +587,33 @@ static sdq_status contract_impl(int64_t m, LinearSet S, const sdq_layout* L, boo
   const sdq_layout* P = L;
   if (needs_unpack(L, m)) {
     P = &F;
-    size_t off = align_up(path_ws_bytes(P, m, digits), 256);
+    const bool form = apart && digits_possible(L, m);
+    if (form) {
+      sdq_status st = launch_digits_to_half(m, P, ws, digits_at(L, m, false), s);
+      if (st != SDQ_OK) return st;
+    }
+    size_t off = align_up(path_ws_bytes(P, m, at), 256);
     for (int j = 0; j < S.count; ++j) {
       sdq_layout Lj = *L;
       Lj.n = S.n[j];
       Lj.n_pad = (S.n[j] + kPanel - 1) / kPanel * kPanel;
       uint32_t* fields = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + off);
-      sdq_status st = launch_unpack_base3(S.codes[j], &Lj, fields, s);
+      sdq_status st = launch_unpack_base3(S.codes[j], &Lj, fields, form ? prefill_form(ws, m) : nullptr, s);
       if (st != SDQ_OK) return st;
       S.codes[j] = fields;
       off = align_up(off + fields_codes_bytes(&Lj), 256);
     }
   }
-  if (digits) {   // the rest of the workspace holds the partial sums of a split contraction
-    const size_t own = align_up(set_ws_bytes(L, S.n, S.count, m, true), 256);
-    return launch_digit_contract(m, S, P, accumulate, ws, static_cast<char*>(ws) + own,
-                                 ws_bytes > own ? ws_bytes - own : 0, s);
+  if (m <= 16) return launch_decode_contract(m, S, P, accumulate, ws, !apart, s);
+  const bool by_form = apart && !needs_unpack(L, m) && digits_possible(L, m);
+  if (by_form) at = digits_at(L, m, false);
+  if (at) {   // the rest of the workspace holds the partial sums of a split contraction
+    const size_t own = align_up(set_ws_bytes(L, S.n, S.count, m, at), 256);
+    sdq_status st = launch_digit_contract(m, S, P, accumulate, ws, at, static_cast<char*>(ws) + own,
+                                          ws_bytes > own ? ws_bytes - own : 0, by_form, s);
+    if (st != SDQ_OK || !by_form) return st;
   }
-  return m <= 16 ? launch_decode_contract(m, S, P, accumulate, ws, y_ready, s)
-                 : launch_prefill_contract(m, S, P, accumulate, ws, s);
+  return launch_prefill_contract(m, S, P, accumulate, ws, by_form, s);
 }
 
 static LinearSet single_set(const void* codes, const float* scales, const sdq_layout* L, float* y) {
@@ -612,8 +638,7 @@ sdq_status sdq_linear_expanded(int64_t m, const void* codes, const float* scales
                                size_t ws_bytes, void* stream) {
   sdq_status st = linear_common(L, m, ws_bytes, ws);
   if (st != SDQ_OK || m == 0 || L->n == 0) return st;
-  return contract_impl(m, single_set(codes, scales, L, y), L, accumulate != 0, ws, ws_bytes,
-                       use_digits(L, m, nullptr, ws_bytes), false, stream);
+  return contract_impl(m, single_set(codes, scales, L, y), L, accumulate != 0, ws, ws_bytes, 0, true, stream);
 }
 
 // Argument checks of sdq_linear that precede the workspace check.
@@ -634,13 +659,13 @@ static sdq_status linear_args(const void* x, sdq_dtype xt, int64_t m, const void
 // will add into it.
 static sdq_status run_set(const void* x, sdq_dtype xt, int64_t m, const LinearSet& S, const sdq_layout* L,
                           int32_t accumulate, void* ws, size_t ws_bytes, void* stream, bool may_allocate) {
-  const bool digits = use_digits(L, m, &S, ws_bytes);
+  const size_t at = use_digits(L, m, &S, ws_bytes, !may_allocate);
   const sdq_layout F = fields_view(L);
   const sdq_layout* P = needs_unpack(L, m) ? &F : L;
   const bool zero_in_expand = !accumulate && m <= 16 && decode_needs_zero_y(P, m, set_panels(S));
-  sdq_status st = expand_impl(x, xt, m, L, ws, zero_in_expand ? &S : nullptr, digits, stream, may_allocate);
+  sdq_status st = expand_impl(x, xt, m, L, ws, zero_in_expand ? &S : nullptr, at, stream, may_allocate);
   if (st != SDQ_OK) return st;
-  return contract_impl(m, S, L, accumulate != 0, ws, ws_bytes, digits, true, stream);
+  return contract_impl(m, S, L, accumulate != 0, ws, ws_bytes, at, false, stream);
 }
 
 }  // extern "C"
@@ -733,8 +758,7 @@ sdq_status sdq_linear_group_expanded(int64_t m, int32_t count, const void* const
   LinearSet S;
   sdq_status st = group_set(m, count, codes, scales, layouts, y, ws_bytes, ws, &S);
   if (st != SDQ_OK || m == 0 || S.count == 0) return st;
-  return contract_impl(m, S, &layouts[0], accumulate != 0, ws, ws_bytes,
-                       use_digits(&layouts[0], m, nullptr, ws_bytes), false, stream);
+  return contract_impl(m, S, &layouts[0], accumulate != 0, ws, ws_bytes, 0, true, stream);
 }
 
 // ---------------------------------------------------------------------------

@@ -97,8 +97,10 @@ sdq_status launch_quantize(const float* w, const sdq_layout* L, const Tables* T,
 // Base-3 bytes of a ternary layout L from its codes as 2-bit fields (the
 // layout fields_view(L)).
 sdq_status launch_repack_base3(const uint32_t* fields, const sdq_layout* L, void* codes, hipStream_t stream);
-// The inverse: 2-bit fields (fields_view(L)) from base-3 codes.
-sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t* fields, hipStream_t stream);
+// The inverse: 2-bit fields (fields_view(L)) from base-3 codes.  form (or NULL):
+// a workspace's form word, made positive (fp16 x_tilde, see prefill_form).
+sdq_status launch_unpack_base3(const void* codes, const sdq_layout* L, uint32_t* fields, float* form,
+                               hipStream_t stream);
 // Encode blocks b0 .. b0 + nbl - 1 from w (row stride ldw; column 0 of w is the
 // first column of block b0; fp64 weights are rounded to fp32): rotate and upsample fold their row maxima into
 // rmax_acc, the scan uses the row scales in rmax_scale (one buffer for a plain
@@ -155,25 +157,37 @@ sdq_status launch_decode_contract(int64_t m, LinearSet set, const sdq_layout* L,
                                   bool y_ready, hipStream_t stream);
 
 // Prefill path (m > 16) on fp16 x_tilde: expansion, then MFMA GEMM.  Layouts
-// without Had keep x_tilde as an fp16 pair (prefill_split).  The workspace:
-// the fp16 x_tilde plane(s) (prefill_planes_bytes), then the per-row powers of
-// two p_i [m] and 1 / p_i [m] (fp32) that keep x_tilde inside fp16's range.
+// without Had keep x_tilde as an fp16 pair (prefill_split).  The workspace: the
+// per-row powers of two p_i [m] and 1 / p_i [m] (fp32) that keep x_tilde inside
+// fp16's range (prefill_fac_bytes), then the fp16 x_tilde plane(s).
+//
+// The form word.  Layouts with Had have two forms of x_tilde, and an expansion and a
+// contraction called apart need not be given the same workspace size, so what an
+// expansion wrote is told by the workspace itself: word m (prefill_form) is 1 / p_0,
+// positive, in front of fp16 x_tilde and negative where digit planes (below) were
+// written.  A contraction called apart launches both GEMMs with the word's address
+// (`form`), and the one whose x_tilde is not there returns at once.
 bool prefill_split(const sdq_layout* L);
-size_t prefill_planes_bytes(const sdq_layout* L, int64_t m);
+inline size_t prefill_fac_bytes(int64_t m) { return (static_cast<size_t>(m) * 2 * sizeof(float) + 255) / 256 * 256; }
+inline float* prefill_form(void* ws, int64_t m) { return static_cast<float*>(ws) + m; }
 size_t prefill_ws_bytes(const sdq_layout* L, int64_t m);
-// digits: write x_tilde as digit planes (below) instead of fp16.
+// digits_at: write x_tilde as digit planes from that byte of the workspace on; 0: fp16.
 sdq_status launch_prefill_expand(const void* x, sdq_dtype xt, int64_t m, const sdq_layout* L,
-                                 const Tables* T, void* ws, bool digits, hipStream_t stream);
+                                 const Tables* T, void* ws, size_t digits_at, hipStream_t stream);
+// by_form: only if the workspace holds fp16 x_tilde.
 sdq_status launch_prefill_contract(int64_t m, LinearSet set, const sdq_layout* L, bool accumulate, void* ws,
-                                   hipStream_t stream);
+                                   bool by_form, hipStream_t stream);
 
 // Prefill on digit planes (layouts with Had): x_tilde as three FP6 planes with a
 // power-of-two scale per 32 samples, as operand images of the FP6 x FP4 matrix
 // cores.  A K step holds 64 samples (their number is rounded up to two, the
 // samples past k_up are zero); rows come in groups of 32.
-//   planes   [n_steps][n_rg][kDigitTile]: per plane 64 lanes x 16 bytes, then
-//            64 lanes x 8 bytes, then 64 block exponents (biased by 127)
-//   row_fac  the row factors p_i and 1 / p_i of the expansions that need them
+//   row_fac  the row factors p_i and 1 / p_i of the expansions that need them, and the
+//            form word, at the workspace's start
+//   planes   [n_steps][n_rg][kDigitTile], `at` bytes into the workspace: per plane 64
+//            lanes x 16 bytes, then 64 lanes x 8 bytes, then 64 block exponents
+//            (biased by 127)
+//   bytes    the workspace up to the planes' end
 constexpr int kDigitPlane = 1536, kDigitTile = 3 * kDigitPlane + 64;
 constexpr int64_t kDigitMaxK = int64_t{1} << 25;   // k_up: a tile's codes are addressed with 32 bits
 struct DigitPlanes {
@@ -182,7 +196,10 @@ struct DigitPlanes {
   int64_t n_rg = 0, n_steps = 0;
   size_t bytes = 0;
 };
-DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws);
+DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws, size_t at);
+// If the workspace holds digit planes (of ternary codes) from byte `at` on, which lies past
+// the fp16 x_tilde: fp16 x_tilde from them, all but the form word's sign.
+sdq_status launch_digits_to_half(int64_t m, const sdq_layout* L, void* ws, size_t at, hipStream_t stream);
 // How the contraction of `count` linears of n[j] rows is cut: the tile shape (an
 // index of the contraction's own), K in `splits` parts of steps_per steps, with
 // part_bytes of partial sums (at most the bytes given).
@@ -191,8 +208,9 @@ struct DigitPlan {
   size_t part_bytes = 0;
 };
 DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes);
-sdq_status launch_digit_contract(int64_t m, LinearSet set, const sdq_layout* L, bool accumulate, void* ws,
-                                 void* part_ws, size_t part_bytes, hipStream_t stream);
+// by_form: only if the workspace holds digit planes.
+sdq_status launch_digit_contract(int64_t m, LinearSet set, const sdq_layout* L, bool accumulate, void* ws, size_t at,
+                                 void* part_ws, size_t part_bytes, bool by_form, hipStream_t stream);
 
 // Block compensation (Algorithm 1's block loop), fp64.
 sdq_status launch_hessian_accumulate(const float* x, int64_t m, int64_t k, double* h, hipStream_t stream);

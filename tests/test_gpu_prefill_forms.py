@@ -1,0 +1,100 @@
+"""Separate expansions and contractions at m > 16 rows: x_tilde lies in the workspace as digit planes
+or in fp16, and a contraction reads what is there -- whatever sufficient workspace sizes the two
+calls are given, and after a whole call (sdq_linear, sdq_linear_group) as after an expansion."""
+import itertools
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import layout as LY
+from oracle import linear as OL
+from tests.gpu_common import TOL, require_gpu, to_device_x
+
+pytestmark = pytest.mark.gpu
+
+N, OTHER, K, M = 203, 519, 1024, 40
+
+
+def _linear(torch, P, n, levels, packing, block, osr):
+    L = P.sdq_layout_init(n, K, osr, levels, block)
+    rng = np.random.default_rng(n + levels)
+    codes = rng.integers(-1, 2, size=(n, L.k_up), dtype=np.int8) if levels == 3 else \
+        (2 * rng.integers(0, 2, size=(n, L.k_up), dtype=np.int8) - 1)
+    buf = LY.pack(codes, levels)
+    if packing:
+        P.sdq_layout_set_packing(L, packing)
+        buf = LY.pack_base3(codes)
+    scales = rng.uniform(0.01, 0.02, n).astype(np.float32)
+    return P.Encoded(L, torch.from_numpy(buf).cuda(), torch.from_numpy(scales).cuda()), codes, scales
+
+
+def _least(L, m):
+    """One fp16 x_tilde, its row factors and, for base-3 codes, their 2-bit copy."""
+    per = 128 if L.levels == 2 else 64
+    chunks = -(-L.k_up // per)
+    up = lambda b: -(-b // 256) * 256                                      # noqa: E731
+    copy = L.n_pad * chunks * 16 if L.packing else 0
+    return up(2 * m * chunks * per) + up(8 * m) + up(copy)
+
+
+CASES = pytest.mark.parametrize("levels,packing,block,osr,dtype", [
+    (2, 0, 256, 1.5, "f16"), (3, 0, 256, 1.625, "bf16"), (3, 1, 256, 1.625, "f16"),
+    (3, 0, 64, 2.5, "f32"), (3, 1, 128, 1.25, "f32")])
+
+
+def _setup(levels, packing, block, osr, dtype):
+    torch = require_gpu()
+    import paper_2510_03275_amd as P
+    made = [_linear(torch, P, n, levels, packing, block, osr) for n in (N, OTHER)]
+    x, x64 = to_device_x(synth.activations_f32(levels + block, 8, M, K), dtype, torch)
+    want = [OL.linear_fp64(x64, c, s, block, e.layout.m_up) for e, c, s in made]
+
+    def check(y, j):
+        err = OL.rel_err_rows(y.cpu().numpy().astype(np.float64), want[j])
+        assert np.all(err <= TOL), err.max()
+    return torch, P, [e for e, _, _ in made], x, check
+
+
+@CASES
+def test_expansion_and_contraction_of_different_sizes(levels, packing, block, osr, dtype):
+    torch, P, encs, x, check = _setup(levels, packing, block, osr, dtype)
+    L = encs[1].layout
+    sizes = (_least(L, M), P.sdq_linear_workspace_bytes(L, M))
+    assert sizes[0] < sizes[1]
+    for a, b in itertools.product(sizes, sizes):
+        ws = torch.full((sizes[1],), 0x7F, dtype=torch.uint8, device="cuda")
+        P.sdq_expand_activations(x, L, ws[:a])
+        for j in (1, 0):
+            y = torch.full((M, encs[j].layout.n), float("nan"), device="cuda")
+            P.sdq_linear_expanded(M, encs[j].codes, encs[j].scales, encs[j].layout, y, ws[:b])
+            check(y, j)
+
+
+@CASES
+def test_contraction_after_a_whole_call(levels, packing, block, osr, dtype):
+    torch, P, encs, x, check = _setup(levels, packing, block, osr, dtype)
+    first, other = encs
+    sizes = (_least(other.layout, M), P.sdq_linear_workspace_bytes(other.layout, M))
+    for a, b in itertools.product(sizes, sizes):
+        ws = torch.full((sizes[1],), 0x7F, dtype=torch.uint8, device="cuda")
+        y = torch.full((M, N), float("nan"), device="cuda")
+        P.sdq_linear(x, first.codes, first.scales, first.layout, y, ws[:a])
+        check(y, 0)
+        for _ in range(2):
+            y = torch.full((M, OTHER), float("nan"), device="cuda")
+            P.sdq_linear_expanded(M, other.codes, other.scales, other.layout, y, ws[:b])
+            check(y, 1)
+    # a group call leaves its expansion too
+    ys = [torch.full((M, e.layout.n), float("nan"), device="cuda") for e in encs]
+    group = P.LinearGroup(encs, ys)
+    ws = torch.full((P.sdq_linear_group_workspace_bytes([e.layout for e in encs], M),), 0x7F, dtype=torch.uint8,
+                    device="cuda")
+    P.sdq_linear_group(x, group, ws)
+    for y in ys:
+        y.fill_(float("nan"))
+    P.sdq_linear_group_expanded(M, group, ws)
+    for j in (0, 1):
+        check(ys[j], j)
+    P.sdq_linear_expanded(M, first.codes, first.scales, first.layout, ys[0], ws)
+    check(ys[0], 0)
