@@ -233,6 +233,8 @@ def sdq_linear_workspace_bytes(layout: sdq_layout, m: int) -> int:
 
 def sdq_linear(x, codes, scales, layout: sdq_layout, y, workspace, stream=None,
                accumulate: bool = False) -> None:
+    if not isinstance(layout, sdq_layout):     # its address is passed on as it is
+        raise ctypes.ArgumentError(f"layout is a {type(layout).__name__}, not an sdq_layout")
     shape = x.shape
     status = _call_linear(x.data_ptr(), _DTYPES[x.dtype], shape[0] if len(shape) == 2 else 0,
                           None if codes is None else codes.data_ptr(), None if scales is None else scales.data_ptr(),

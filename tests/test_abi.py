@@ -319,3 +319,14 @@ def test_group_entry_point_validates_before_gpu_work():
     assert lib.sdq_linear_group(fake, 0, 1, 0, ptrs, ptrs, arr, ptrs, 0, fake, 1 << 30, None) == -1
     assert lib.sdq_linear_group(fake, 0, 1, 2, ptrs, ptrs, arr, ptrs, 0, fake, 16, None) == -6
     assert lib.sdq_linear_group(fake, 0, 0, 2, ptrs, ptrs, arr, ptrs, 0, None, 0, None) == 0   # m = 0
+
+
+@pytest.mark.parametrize("wrong", [lambda L: ctypes.pointer(L), lambda L: (ctypes.c_char * 16)(), lambda L: None])
+def test_linear_refuses_what_is_not_a_layout(wrong):
+    # the binding passes addresses: a pointer object or a short buffer must not be read as a layout
+    torch = pytest.importorskip("torch")
+    import types
+    x = torch.zeros(1, 256, dtype=torch.float16)
+    L = P.sdq_layout_init(64, 256, 2.0, 3)
+    with pytest.raises((ctypes.ArgumentError, TypeError)):
+        P.sdq_linear(x, x, x, wrong(L), x, x, stream=types.SimpleNamespace(cuda_stream=0))
