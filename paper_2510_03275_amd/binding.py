@@ -18,6 +18,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsdq.so")
 
 SDQ_OK = 0
+SDQ_ERR_WORKSPACE = -6
 SDQ_F16, SDQ_BF16, SDQ_F32 = 0, 1, 2
 SDQ_HAD_NONE, SDQ_HAD_SYLVESTER, SDQ_HAD_SIGNED = 0, 1, 2
 SDQ_PACK_FIELDS, SDQ_PACK_BASE3 = 0, 1
@@ -464,7 +465,10 @@ def quantize_compensated(w, osr: float, levels: int, u, block: int = 256, check:
 def linear(x, enc: Encoded, workspace=None, out=None, stream=None, accumulate: bool = False):
     """y = x W_hat^T for a device activation [m, k] (fp16, bf16 or fp32).
 
-    With accumulate=True the product is added into `out` (which must be given).
+    With accumulate=True the product is added into `out` (which must be given).  A
+    workspace is used if the call accepts it (sdq_linear: also less than
+    sdq_linear_workspace_bytes); without one, or with one too small, the call
+    allocates its own.
     """
     layout = enc.layout
     shape = x.shape
@@ -474,8 +478,13 @@ def linear(x, enc: Encoded, workspace=None, out=None, stream=None, accumulate: b
     if accumulate and out is None:
         raise ValueError("accumulate=True needs out")
     y = out if out is not None else torch.empty((m, layout.n), dtype=torch.float32, device=x.device)
-    need = _call_workspace(_addr(layout), m)
-    if workspace is None or workspace.nbytes < need:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x.device)
+    if workspace is not None:
+        try:
+            sdq_linear(x, enc.codes, enc.scales, layout, y, workspace, stream, accumulate)
+            return y
+        except SdqError as e:          # raised before anything is launched
+            if e.status != SDQ_ERR_WORKSPACE:
+                raise
+    workspace = torch.empty(max(_call_workspace(_addr(layout), m), 1), dtype=torch.uint8, device=x.device)
     sdq_linear(x, enc.codes, enc.scales, layout, y, workspace, stream, accumulate)
     return y

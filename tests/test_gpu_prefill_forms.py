@@ -98,3 +98,19 @@ def test_contraction_after_a_whole_call(levels, packing, block, osr, dtype):
         check(ys[j], j)
     P.sdq_linear_expanded(M, first.codes, first.scales, first.layout, ys[0], ws)
     check(ys[0], 0)
+
+
+@CASES
+def test_linear_runs_in_any_sufficient_workspace(levels, packing, block, osr, dtype):
+    # P.linear allocates nothing where the call accepts the workspace that it is given
+    torch, P, (enc, _), x, check = _setup(levels, packing, block, osr, dtype)
+    need = _least(enc.layout, M)
+    ws = torch.empty(P.sdq_linear_workspace_bytes(enc.layout, M), dtype=torch.uint8, device="cuda")
+    y = torch.empty(M, N, device="cuda")
+    for size, own in ((need, False), (ws.numel() - 1, False), (ws.numel(), False), (need - 1, True)):
+        y.fill_(float("nan"))
+        part = ws[:size]
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        P.linear(x, enc, workspace=part, out=y)
+        assert (torch.cuda.memory_stats()["allocation.all.allocated"] > before) == own, size
+        check(y, 0)
