@@ -79,19 +79,22 @@ def _build_synth() -> str:
     return SYNTH_LIB
 
 
-PYCALL = os.path.join(HERE, "_sdqcall.so")
+# Named for this interpreter's ABI, so that no other one loads it.
+PYCALL = os.path.join(HERE, "_sdqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def _build_pycall() -> None:
-    """The binding's native calls (csrc/pycall.c), where Python's headers are
-    installed; the binding uses ctypes without it."""
+    """The binding's native calls (csrc/pycall.c), where a C compiler and
+    Python's headers are installed; the binding uses ctypes without them."""
+    for old in {PYCALL, os.path.join(os.path.dirname(PYCALL), "_sdqcall.so")}:
+        if os.path.exists(old):
+            os.remove(old)
     inc = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(inc, "Python.h")):
-        if os.path.exists(PYCALL):
-            os.remove(PYCALL)
+    gcc = shutil.which("gcc")
+    if gcc is None or not os.path.exists(os.path.join(inc, "Python.h")):
         return
     tmp = PYCALL + ".tmp"
-    cmd = ["gcc", "-O2", "-fPIC", "-shared", "-Wall", f"-I{inc}", os.path.join(CSRC, "pycall.c"), "-o", tmp]
+    cmd = [gcc, "-O2", "-fPIC", "-shared", "-Wall", f"-I{inc}", os.path.join(CSRC, "pycall.c"), "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"pycall build failed: {' '.join(cmd)}\n{res.stdout}\n{res.stderr}")
