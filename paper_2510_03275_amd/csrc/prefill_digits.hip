@@ -98,11 +98,13 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 // tile stopped after its first eight steps: 38 us, against 8 without the code
 // loads, 9 without the copies and 17 with both through LDS) and took the
 // registers of four steps; whole calls differ by a few per cent.
-template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D>
+// APART: a contraction called apart, which returns if fp16 x_tilde is there (a template
+// parameter, since the test in front of everything else cost a whole call 0.4 us).
+template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D, bool APART>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
     int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part, const float* form) {
-  if (form && !(*form < 0.0f)) return;             // a contraction called apart: fp16 x_tilde is there
+  if (APART && !(*form < 0.0f)) return;
   constexpr int RG = WM * RT;
   constexpr int W = WM * WN;
   constexpr int BN = 32 * CT * WN;                 // weight rows of the tile
@@ -296,11 +298,11 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
 }
 
 // y (+)= the sum of a linear's partial sums, in the order of the splits.  V
-// floats per thread and load (4 where y is 16-byte aligned).
-template <int V>
+// floats per thread and load (4 where y is 16-byte aligned).  APART as above.
+template <int V, bool APART>
 __global__ __launch_bounds__(256) void reduce_digits_kernel(LinearSet S, DigitParts part, int64_t m, int splits,
                                                             int accumulate, const float* form) {
-  if (form && !(*form < 0.0f)) return;
+  if (APART && !(*form < 0.0f)) return;
   const int lin = blockIdx.y;
   const int64_t cnt = m * S.n[lin];
   const float* __restrict__ src = part.base + part.off[lin];
@@ -443,7 +445,7 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
 #define SDQ_DIG(LV, I, WM, WN, RT, CT, MINW, D)                                                           \
   case I:                                                                                                \
     static_assert(kShapes[I].rg == WM * RT && kShapes[I].bn == 32 * WN * CT, "shape");                   \
-    gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, D><<<grid, dim3(64 * WM * WN), 0, stream>>>(            \
+    gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, D, APART><<<grid, dim3(64 * WM * WN), 0, stream>>>(     \
         d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,              \
         plan.steps_per, acc, part, form);                                                                \
     break
@@ -453,11 +455,16 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
     SDQ_DIG(LV, 1, 1, 4, 2, 4, 2, 4);                                                                    \
     SDQ_DIG(LV, 2, 2, 4, 2, 4, 2, 5);                                                                    \
   }
-  if (L->levels == 2) {
-    SDQ_DIG_SHAPES(2)
-  } else {
-    SDQ_DIG_SHAPES(3)
-  }
+  auto gemm = [&](auto apart) {
+    constexpr bool APART = decltype(apart)::value;
+    if (L->levels == 2) {
+      SDQ_DIG_SHAPES(2)
+    } else {
+      SDQ_DIG_SHAPES(3)
+    }
+  };
+  if (by_form) gemm(std::true_type{});
+  else gemm(std::false_type{});
 #undef SDQ_DIG_SHAPES
 #undef SDQ_DIG
   if (plan.splits > 1) {
@@ -470,8 +477,9 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
     const int v = al ? 4 : 1;
     const dim3 rgrid(static_cast<unsigned>(std::min<int64_t>((most + 256 * v - 1) / (256 * v), 4096)),
                      static_cast<unsigned>(S.count));
-    if (al) reduce_digits_kernel<4><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0, form);
-    else reduce_digits_kernel<1><<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0, form);
+    auto reduce = al ? (by_form ? reduce_digits_kernel<4, true> : reduce_digits_kernel<4, false>)
+                     : (by_form ? reduce_digits_kernel<1, true> : reduce_digits_kernel<1, false>);
+    reduce<<<rgrid, dim3(256), 0, stream>>>(S, part, m, plan.splits, accumulate ? 1 : 0, form);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "digit-plane GEMM launch");

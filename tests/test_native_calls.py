@@ -78,8 +78,10 @@ def test_ctypes_calls_give_the_same_results(monkeypatch, m):
             torch.cuda.current_stream().wait_stream(torch.cuda.default_stream())
             out.append([P.linear(x, enc), *ys])
         torch.cuda.synchronize()
+    # one row: the parts of K (a few) are added to y in any order, 2^-24 of the largest per add
+    bound = 1e-6 if m == 1 else 0.0
     for a, b in zip(*out):
-        assert torch.equal(a, b)
+        assert torch.max(torch.abs(a - b)).item() <= bound * torch.max(torch.abs(a)).item()
 
 
 def test_module_is_named_for_this_interpreter():
