@@ -1608,11 +1608,12 @@ bool mfma_lds(const sdq_layout* L, int64_t m, int64_t panels) {
 // on, the longer-lived waves of two blocks each win (m = 16: 64 -> 56 us on
 // 28672 x 8192, 72 -> 59 us on 8192 x 28672; m = 12 o_proj 21.7 -> 19.5 us),
 // while launches whose workgroups at one block per wave all fit the chip at once
-// are short of waves: one against two blocks at m = 16, 256 workgroups (LLaMA-7B
-// o_proj, OSR 2.125) 9.2 against 12.2 us, 704 (down_proj, OSR 2.5) 17.6 against
-// 19.0, 768 (q/k/v, OSR 2.25) 17.6 against 22.5, but 1024 (8192 x 8192, OSR 3.25)
-// 31.0 against 25.8 and 1376 (gate/up) 31.4 against 29.4; at m = 12, 1024 still
-// 20.1 against 24.6, 1280 18.3 against 17.6.
+// are short of waves.  Time at one block over time at two of whole calls (k = 4096,
+// 8192, 11008 at OSR 2 to 3, 9-16 rows), by workgroups per CU at one block:
+//   four plane groups (13-16 rows)  up to 3: 0.75-1.00, 3.2-4: 0.92-1.18
+//   three, batches of four steps    up to 3: 0.75-0.87, 3.2-3.5: 0.94-0.98, 4: 1.02-1.11
+//   three, smaller batches          up to 4: 0.74-1.00 (4: 0.83-0.94), 4.3-5.4: 0.91-1.05
+//   base-3, three or four           up to 3: 0.74-1.00, 3.2-4: 1.05-1.13 (0.85 at k = 11008)
 int mfma_bpw(const sdq_layout* L, int64_t m, int64_t panels) {
   static const char* env = std::getenv("SDQ_MFMA_BPW");
   if (env) {
@@ -1621,7 +1622,11 @@ int mfma_bpw(const sdq_layout* L, int64_t m, int64_t panels) {
   }
   const int npg = npg_for(m);
   if (npg <= 2) return 1;
-  if (panels * ((L->nb + 3) / 4) <= (npg == 3 ? 1024 : 768)) return 1;
+  const bool b3 = mfma_base3(L, m);
+  int64_t half_wgs = 6;                        // the line, in half workgroups per CU
+  if (npg == 3 && !b3)
+    half_wgs = pick_ch(mfma_cpb(L), npg, L->levels) * (L->levels == 2 ? 2 : 1) >= 4 ? 7 : 8;
+  if (2 * panels * ((L->nb + 3) / 4) <= half_wgs * device_compute_units()) return 1;
   return npg == 3 && mfma_lds(L, m, panels) ? 1 : 2;
 }
 
