@@ -21,11 +21,13 @@
 // accumulator v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A K
 // step is 64 samples.  The digit planes are stored as operand images: per step
 // and 32-row group three planes of 64 lanes x 16 bytes, then 64 lanes x 8
-// bytes, then the 64 block scales, so a tile is copied to LDS as one run and read
-// without conflicts.
+// bytes, then the 64 block scales, so a tile is copied to LDS as one run and a wave
+// reads it as runs of 1024, 512 and 64 bytes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
+#include <cstdlib>
 #include <type_traits>
 
 #include "sdq_internal.h"
@@ -90,9 +92,9 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 
 // WM x WN waves, each RT x CT accumulator tiles of 32 x 32: a workgroup tile of
 // RG = WM RT row groups (32 activation rows each) x 256 weight rows, over the
-// K steps of its split.  The step's x_tilde tile and its codes (four panels, 64
-// rows x 16 bytes each) come straight from global memory to a ring of D LDS
-// buffers, D - 1 steps ahead; one plain barrier per step with a counted wait, so
+// K steps of its split.  The step's x_tilde tile and its codes (BN / 64 panels, 64
+// rows x 16 bytes each) come straight from global memory to a ring of kRing LDS
+// buffers, kRing - 1 steps ahead; one plain barrier per step with a counted wait, so
 // that the copies of the following steps stay in flight.  Codes loaded to
 // registers between the copies to LDS held up a workgroup's start (a 64 x 256
 // tile stopped after its first eight steps: 38 us, against 8 without the code
@@ -100,7 +102,8 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 // registers of four steps; whole calls differ by a few per cent.
 // APART: a contraction called apart, which returns if fp16 x_tilde is there (a template
 // parameter, since the test in front of everything else cost a whole call 0.4 us).
-template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, int D, bool APART>
+constexpr int kRing = 4;
+template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, bool APART>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
     int64_t m_tiles, int64_t n_tiles, int steps_per, int accumulate, DigitParts part, const float* form) {
@@ -115,9 +118,8 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
   constexpr int FC = (NC + W - 1) / W;             // copies per wave
   constexpr int TB = (NC + (NC % W ? 1 : 0)) * 1024;   // LDS bytes per buffer (the last KB takes the surplus copies)
   constexpr int CODES = NX * 1024;                 // the codes' place in it
-  static_assert((D - 2) * FC <= 63, "vmcnt range");
-  static_assert(D >= 3 && D <= 5, "ring size");
-  auto ring = [](auto jc) { return ring_buffer<TB, decltype(jc)::value % D>(); };
+  static_assert((kRing - 2) * FC <= 63, "vmcnt range");
+  auto ring = [](auto jc) { return ring_buffer<TB, decltype(jc)::value % kRing>(); };
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int half = lane / 32;
@@ -169,11 +171,11 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
                                        (dig_lds_ptr)(buf + 1024 * min(cj, NC)), 16, 0, 0);
     }
   };
-  // Wait until at most D - 2 steps' copies of this wave are outstanding, then for
+  // Wait until at most kRing - 2 steps' copies of this wave are outstanding, then for
   // every wave: the next step's are there.  Nothing is scheduled across it.
   auto landed = [&]() {
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * FC));
+    __builtin_amdgcn_s_waitcnt(wait_vm((kRing - 2) * FC));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     products(0);
     read(2);
     __builtin_amdgcn_sched_barrier(0);
-    fill(ring(std::integral_constant<int, J + D - 1>{}), it + D - 1);
+    fill(ring(std::integral_constant<int, J + kRing - 1>{}), it + kRing - 1);
     products(1);
     products(2);
     landed();
@@ -245,28 +247,19 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
   __builtin_amdgcn_sched_barrier(0);
   fill(ring(J1{}), it0 + 1);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (D >= 4) fill(ring(J2{}), it0 + 2);
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (D >= 5) fill(ring(J3{}), it0 + 3);
+  fill(ring(J2{}), it0 + 2);
   landed();
+  static_assert(kRing == 4, "steps of a round");
   int it = it0;
-  for (const int whole = it0 + n_it / D * D; it < whole; it += D) {
+  for (const int whole = it0 + n_it / kRing * kRing; it < whole; it += kRing) {
     step(J0{}, it);
     step(J1{}, it + 1);
     step(J2{}, it + 2);
-    if constexpr (D >= 4) step(J3{}, it + 3);
-    if constexpr (D >= 5) step(std::integral_constant<int, 4>{}, it + 4);
+    step(J3{}, it + 3);
   }
-  const int rest = it0 + n_it - it;
-  if (rest > 0) {
+  if (n_it % kRing) {                              // n_it is even
     step(J0{}, it);
-    if (rest > 1) {
-      step(J1{}, it + 1);
-      if (D >= 4 && rest > 2) {
-        step(J2{}, it + 2);
-        if (D >= 5 && rest > 3) step(J3{}, it + 3);
-      }
-    }
+    step(J1{}, it + 1);
   }
   // the last copies (never read) land before the workgroup's LDS is released
   __builtin_amdgcn_s_waitcnt(0);
@@ -343,12 +336,12 @@ __global__ __launch_bounds__(256) void reduce_digits_kernel(LinearSet S, DigitPa
 // several run.  Fitted, as are the costs of the partial sums below, to 3700
 // timings of contractions on MI355X (12 groups of linears with k_up 960 to 24576
 // and 700 to 28672 rows, m 17 to 2048, 1 to 16 splits): within 6 % for half of
-// them; the plan chosen is 2.2 % slower than the best of the three shapes and all
-// splits on average, 14 % at most.  Of nine shapes timed these three are within
-// 0.5 % of the best of all on average: 32 x 256 (many short tiles) up to a few
-// hundred rows, 128 x 512 for large products (28672 x 16384 at m = 2048: 1196 us,
-// 64 x 512 1204, 128 x 256 1266, 256 x 256 1308, 32 x 256 1438), where wide
-// tiles matter because x_tilde takes nine times the bytes of the codes.
+// them (17-20 % low on the largest, where it does not matter to the choice).  Of
+// nine shapes timed: 32 x 256 (many short tiles) up to a few hundred rows, 64 x
+// 512 for large products (28672 x 16384 at m = 2048: 1204 us, 128 x 512 with a
+// ring of five 1196, 128 x 256 1266, 256 x 256 1308, 32 x 256 1438), where wide
+// tiles matter because x_tilde takes nine times the bytes of the codes.  128 x 512
+// fills a CU's LDS with one workgroup, and the fit chose it next to never.
 struct DigitShape {
   int rg, bn, per_cu;
   double step_us, step_each_us;
@@ -356,8 +349,8 @@ struct DigitShape {
 constexpr DigitShape kShapes[] = {
     {1, 256, 4, 0.273, 0.170},  // 4 waves, each 32 x 64
     {2, 512, 2, 0.680, 0.534},  // 4 waves, each 64 x 128
-    {4, 512, 1, 1.137, 1.137},  // 2 x 4 waves, each 64 x 128
 };
+constexpr int kShapeCount = static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0]));
 
 // Estimated time of a plan (up to a constant).
 double digit_plan_us(const DigitShape& s, int sp, int64_t tiles, int64_t steps, double outs, int64_t cus) {
@@ -391,7 +384,8 @@ DigitPlanes digit_planes(const sdq_layout* L, int64_t m, void* ws, size_t at) {
   return d;
 }
 
-// The split of the contraction.
+// The split of the contraction.  SDQ_DIGIT_PLAN="shape,splits" asks for a plan (a
+// tuning and test aid, read on every call), where K and the workspace allow it.
 DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_t part_bytes) {
   const int64_t n_rg = (m + 31) / 32, pairs = (k_up + 127) / 128;
   const int64_t cus = device_compute_units();
@@ -400,15 +394,19 @@ DigitPlan digit_plan(const int64_t* n, int count, int64_t k_up, int64_t m, size_
   const size_t one_part = static_cast<size_t>(part_floats(n, count, m)) * sizeof(float);
   DigitPlan best;
   double best_us = 1e30;
-  for (int i = 0; i < static_cast<int>(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
+  int shape = -1, splits = -1;
+  const char* env = std::getenv("SDQ_DIGIT_PLAN");
+  if (env && std::sscanf(env, "%d,%d", &shape, &splits) == 2 && (shape < 0 || shape >= kShapeCount)) shape = -1;
+  for (int i = 0; i < kShapeCount; ++i) {
+    if (shape >= 0 && i != shape) continue;
     const int64_t tiles = (n_rg + kShapes[i].rg - 1) / kShapes[i].rg * column_tiles(n, count, kShapes[i].bn);
     for (int sp = 1; sp <= 16; ++sp) {
       const int64_t per = (pairs + sp - 1) / sp;
-      if (sp > 1 && ((sp - 1) * per >= pairs || tiles * (sp - 1) >= 4 * cus)) continue;
+      if (sp > 1 && ((sp - 1) * per >= pairs || (tiles * (sp - 1) >= 4 * cus && shape < 0))) continue;
       if (sp > 1 && one_part * sp > part_bytes) break;
       const double us = digit_plan_us(kShapes[i], sp, tiles, 2 * per, outs, cus);
-      if (us < best_us) {
-        best_us = us;
+      if (us < best_us || (shape >= 0 && sp == splits)) {
+        best_us = shape >= 0 && sp == splits ? 0.0 : us;
         best.shape = i;
         best.splits = sp;
         best.steps_per = static_cast<int>(2 * per);
@@ -442,18 +440,17 @@ sdq_status launch_digit_contract(int64_t m, LinearSet S, const sdq_layout* L, bo
   }
   const int acc = accumulate && plan.splits == 1 ? 1 : 0;
   const dim3 grid(static_cast<unsigned>(m_tiles * n_tiles * plan.splits));
-#define SDQ_DIG(LV, I, WM, WN, RT, CT, MINW, D)                                                           \
+#define SDQ_DIG(LV, I, WM, WN, RT, CT, MINW)                                                             \
   case I:                                                                                                \
     static_assert(kShapes[I].rg == WM * RT && kShapes[I].bn == 32 * WN * CT, "shape");                   \
-    gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, D, APART><<<grid, dim3(64 * WM * WN), 0, stream>>>(     \
+    gemm_digits_kernel<LV, WM, WN, RT, CT, MINW, APART><<<grid, dim3(64 * WM * WN), 0, stream>>>(        \
         d.planes, S, m, L->n_chunks, d.n_rg, static_cast<int>(d.n_steps), m_tiles, n_tiles,              \
         plan.steps_per, acc, part, form);                                                                \
     break
 #define SDQ_DIG_SHAPES(LV)                                                                               \
   switch (plan.shape) {                                                                                  \
-    SDQ_DIG(LV, 0, 1, 4, 1, 2, 4, 4);                                                                    \
-    SDQ_DIG(LV, 1, 1, 4, 2, 4, 2, 4);                                                                    \
-    SDQ_DIG(LV, 2, 2, 4, 2, 4, 2, 5);                                                                    \
+    SDQ_DIG(LV, 0, 1, 4, 1, 2, 4);                                                                       \
+    SDQ_DIG(LV, 1, 1, 4, 2, 4, 2);                                                                       \
   }
   auto gemm = [&](auto apart) {
     constexpr bool APART = decltype(apart)::value;

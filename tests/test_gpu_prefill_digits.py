@@ -44,7 +44,8 @@ def _check(y, x64, r, block=256, bound=BOUND):
     assert _rel(y, y_ref) <= bound, _rel(y, y_ref)
 
 
-# tiles of 1, 2 and 4 groups of 32 rows, full and partial
+# whole and partial groups of 32 rows (all on 32 x 256 tiles, K split; tests/test_gpu_prefill_plans.py
+# takes the other plans)
 @pytest.mark.parametrize("m", [17, 32, 33, 64, 65, 96, 97, 128, 161, 192, 193, 256, 257])
 @pytest.mark.parametrize("n,k,osr,levels", [(300, 1280, 2.0, 3), (257, 1280, 1.625, 2), (64, 512, 2.125, 3)])
 def test_tile_edges(n, k, osr, levels, m):
@@ -129,8 +130,8 @@ def test_nonfinite_activations_stay_in_their_rows():
     assert torch.equal(P.linear(bad, enc)[~rows], want[~rows])
 
 
-# sizes at which each tile shape is chosen (32 x 256, 64 x 512, 128 x 512), split and unsplit, the
-# last column tile and row tile partial, and a group of linears
+# more rows and columns (unsplit 32 x 256 tiles), the last column tile and row tile partial, and a group
+# of linears
 @pytest.mark.parametrize("ns,k,m,levels", [([9000], 256, 60, 3), ([6100], 512, 700, 2), ([12300], 512, 1500, 3),
                                            ([1300, 4000, 70], 768, 300, 3), ([2100], 4096, 900, 2)])
 def test_tile_shapes_and_groups(ns, k, m, levels):
