@@ -37,7 +37,7 @@ constexpr int kUpBM = 128;        // rows per upsample tile (two panels)
 constexpr int kUpBN = 64;         // non-impulse samples per upsample tile
 constexpr int kUpBK = 16;         // t-chunk staged in LDS (two buffers)
 constexpr int kUpThreads = 128;   // 16 x 8 threads, 8 x 8 outputs each
-constexpr int64_t kUpSmall = 1024;   // tiles of 128 x 64 from which a launch uses them
+constexpr int64_t kUpLargePerCu = 4;   // tiles of 128 x 64 per CU from which a launch uses them
 constexpr int kScanWaves = 4;
 
 __global__ void clear_kernel(uint32_t* __restrict__ flag, uint32_t* __restrict__ rmax, int64_t n) {
@@ -595,8 +595,12 @@ static sdq_status encode_blocks(const W* w, int64_t ldw, int64_t b0, int64_t nbl
   }
 #undef SDQ_ROT
   if (T->m_nz > 0) {
-    // The small tile below kUpSmall workgroups of the large one.
-    const bool small = n_ws / kUpBM * (T->m_nz_pad / kUpBN) * nbl < kUpSmall;
+    // The small tile below kUpLargePerCu workgroups of the large one per CU.  Time of whole
+    // encodings with the small tile over that with the large one, by large tiles:
+    // blocks of 256 (OSR 1.5, 2): up to 256 0.50-0.56, 512 0.81, 768 0.93, 1024 and 1536
+    // 1.04-1.08, 2048 0.95, 3200 1.04; OSR 2.75: 320 0.63, 1280 0.93, 2560 0.96, 3840 1.04;
+    // blocks of 128 and 64: 0.56-0.92 up to 1024, 0.86-0.99 up to 3072, then 1.02-1.07.
+    const bool small = n_ws / kUpBM * (T->m_nz_pad / kUpBN) * nbl < kUpLargePerCu * device_compute_units();
     const int f = small ? 2 : 1;
     const dim3 ugrid(static_cast<unsigned>(f * n_ws / kUpBM),
                      static_cast<unsigned>(f * T->m_nz_pad / kUpBN), static_cast<unsigned>(nbl));

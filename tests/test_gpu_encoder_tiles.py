@@ -12,10 +12,13 @@ from tests.gpu_common import require_gpu
 pytestmark = pytest.mark.gpu
 
 
-# tiles of 128 x 64: 1032 (large) and 344, 4, 2 (small); blocks of 128 and 64; n past a tile's end
+# tiles of 128 x 64: 1032, 1080 (large) and 344, 4, 2 (small); blocks of 128 and 64 on both; n past a
+# tile's end
 @pytest.mark.parametrize("n,k,osr,levels,block", [(300, 11008, 3.0, 3, 256), (100, 11008, 3.0, 2, 256),
                                                   (65, 512, 1.5, 3, 256), (129, 256, 2.5, 2, 128),
-                                                  (190, 192, 3.5, 3, 64)])
+                                                  (190, 192, 3.5, 3, 64),
+                                                  (300, 11520, 2.25, 2, 128), (300, 11520, 2.25, 3, 128),
+                                                  (300, 11520, 2.5, 2, 64), (300, 11520, 2.5, 3, 64)])
 def test_codes_are_exact_on_both_tiles(n, k, osr, levels, block):
     torch = require_gpu()
     import paper_2510_03275_amd as P
