@@ -28,9 +28,9 @@ also carries:
                   at m = 1, 4, 16 (workload 3), the three LLaMA-70B linears at
                   m = 1 and at m = 2048 prefill (workload 4), the stack on base-3
                   codes, the encoder (rows/s; the stack's quantization), MultiOSR,
-                  the continuous-precision sweep and Algorithm 1's block
-                  compensation;
-* cpu_baseline -- the CPU oracle on 64 rows of each of the stack's seven linear
+                  the continuous-precision sweep (its rows on stderr) and
+                  Algorithm 1's block compensation;
+* cpu_baseline -- the CPU oracle on 512 rows of each of the stack's seven linear
                   kinds (one mid-depth layer), over a process pool.
 """
 from __future__ import annotations
@@ -405,8 +405,8 @@ def decode_single(torch, P, synth, SG, wl_index, lin_index, m, x_dtype, base3=Fa
 
 
 def prefill_single(torch, P, synth, SG, lin_index, reps: int = 8):
-    """Workload 4 at m = 2048 (bf16 activations): the whole sdq_linear (fp16
-    expansion + MFMA GEMM) and the GEMM alone, 2 m N K_up flops."""
+    """Workload 4 at m = 2048 (bf16 activations): the whole sdq_linear (expansion to
+    digit planes + FP6 x FP4 GEMM) and the contraction called apart, 2 m N K_up flops."""
     wl = synth.workload(4)
     lin = wl.linears[lin_index]
     m = wl.prefill[0]
@@ -812,6 +812,29 @@ def _phase(line, name, fn):
     print(f"[bench] phase {name}: {time.perf_counter() - t:.1f} s", file=sys.stderr, flush=True)
 
 
+def _rounded(obj):
+    """Floats to six digits, in lists and dicts too."""
+    if isinstance(obj, float):
+        return float(f"{obj:.6g}")
+    if isinstance(obj, dict):
+        return {k: _rounded(v) for k, v in obj.items()}
+    if isinstance(obj, list):
+        return [_rounded(v) for v in obj]
+    return obj
+
+
+def _short_line(line):
+    """The line as printed: what stands beside the headline rounded, and the precision
+    sweep's and the ablation's rows by their number (they go to stderr), so that a log that
+    keeps the last 8 KB of the output holds all of it."""
+    out = {k: _rounded(v) if isinstance(v, dict) else v for k, v in line.items()}
+    sweep = out.get("phases", {}).get("precision_sweep", {})
+    for part in (sweep, sweep.get("multiosr_ablation", {})):
+        if "rows" in part:
+            part["rows"] = len(part["rows"])
+    return out
+
+
 def main() -> int:
     ap = argparse.ArgumentParser(description=__doc__.split("\n")[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -934,7 +957,10 @@ def main() -> int:
     if ctx is not None:
         line["cpu_baseline"] = cpu_baseline(ctx, synth, wl, osr)
     line["wall_s"] = time.perf_counter() - t_start
-    print(json.dumps(line), flush=True)
+    sweep = line.get("phases", {}).get("precision_sweep")
+    if sweep:
+        print("[bench] precision_sweep " + json.dumps(_rounded(sweep)), file=sys.stderr, flush=True)
+    print(json.dumps(_short_line(line), separators=(",", ":")), flush=True)
     return 0
 
 

@@ -29,3 +29,16 @@ def test_traffic_scale_from_copy_is_sane():
     # the counters were scaled by a plain copy: both factors near small integers
     assert 0.9 < bench.TRAFFIC_WRITE_SCALE < 1.1
     assert 0.9 < bench.TRAFFIC_FETCH_SCALE < 2.1
+
+
+def test_the_line_keeps_the_headline_and_stays_short():
+    row = {"levels": 3, "had": 1, "osr": 1.25, "bits_per_weight": 2.5, "out_rel_err": 1.2171897665549791,
+           "weight_snr_db": -1.7200476517793215}
+    line = {"metric": "m", "value": 5123.456789012345, "ms_per_step": 8.123456789012345,
+            "config": {"a": 1.23456789, "b": [0.1234567891]},
+            "phases": {"precision_sweep": {"rows": [dict(row) for _ in range(78)], "sweep_s": 0.1234567891}}}
+    out = bench._short_line(line)
+    assert out["value"] == line["value"] and out["ms_per_step"] == line["ms_per_step"]
+    assert out["config"] == {"a": 1.23457, "b": [0.123457]}
+    assert out["phases"]["precision_sweep"] == {"rows": 78, "sweep_s": 0.123457}
+    assert len(line["phases"]["precision_sweep"]["rows"]) == 78       # the line itself is left as it is
