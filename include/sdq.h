@@ -292,10 +292,13 @@ size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
  *   workspace    >= sdq_linear_workspace_bytes(layout, m) bytes, no
  *                initialisation needed.
  * Accuracy: max_r |y - y*| / max_r |y*| <= 1e-3 per activation row against the
- * fp64 definition.  The decode path splits K across workgroups for large
- * layers and then adds the partial sums into y with fp32 atomics, so results
- * may differ between calls in the last bits (relative ~1e-6); the prefill path
- * and unsplit decodes are bitwise deterministic (for one workspace size).  Calls that share a
+ * fp64 definition (m > 16 on digit planes: for rows of x that reach 2^-128).  The
+ * decode path splits K across workgroups (by k and by the panels of the whole
+ * call; at 9 to 16 rows from k = 1280 on at B = 256) and then adds the partial sums
+ * into y with fp32 atomics, so results may differ between calls in the last bits
+ * (relative ~1e-6); unsplit decodes and the prefill path are bitwise
+ * deterministic.  How K is split with m > 16 follows m, the linears of the call
+ * and the workspace size, and the last bits of a row with it.  Calls that share a
  * workspace must be ordered (same stream).
  * Errors: SDQ_ERR_ARG, SDQ_ERR_SHAPE, SDQ_ERR_WORKSPACE, SDQ_ERR_NOMEM, SDQ_ERR_HIP. */
 sdq_status sdq_linear(const void* x_dev, sdq_dtype xt, int64_t m, const void* codes_dev,
@@ -316,7 +319,8 @@ sdq_status sdq_linear(const void* x_dev, sdq_dtype xt, int64_t m, const void* co
  *                  levels, Had and packing (they may differ in n; a linear with
  *                  n = 0 is skipped).
  *   workspace      >= sdq_linear_group_workspace_bytes(layouts, count, m).
- * Results, accuracy and accumulate as sdq_linear for each linear.
+ * Accuracy and accumulate as sdq_linear for each linear; results may differ from
+ * its in the last bits, since K is split by the size of the whole call.
  * Errors: as sdq_linear; SDQ_ERR_ARG also for a count outside 1 .. 4 or
  * layouts that differ in more than n (sdq_linear_group_workspace_bytes
  * returns 0 for those). */

@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(
 // tile (each wave 16 x 32), so that 4096 rows and 256 columns give two workgroups
 // per CU and one multiplies while the other waits for its loads, issued two slices
 // ahead.  A block of 4096 rows and 512 samples: 61 us of passes and product before,
-// 33 with 64 x 64 tiles, 30 so; 16 us at the matrix cores' 77 TFLOP/s.
+// 33 with 64 x 64 tiles, 30 so; 14 us at the matrix cores' 77 TFLOP/s.
 template <int BITS>
 __global__ __launch_bounds__(256) void block_error_kernel(
     const uint32_t* __restrict__ codes, const float* __restrict__ scales, int64_t n, int64_t n_chunks, int64_t j0s,

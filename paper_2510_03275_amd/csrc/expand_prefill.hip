@@ -13,11 +13,13 @@
 //            are written as three FP6 digit planes for the contraction of
 //            prefill_digits.hip (15 bits of fixed point per 32 samples, so the
 //            rounding error is below that of one fp16 rounding: rms 5e-5
-//            against 2e-4 of Gaussian samples).  E takes the whole fp32 range,
-//            so no row factor is needed, and a block with a non-finite sample
-//            gets the scale NaN.
+//            against 2e-4 of Gaussian samples).  E goes from -127 to 126, so
+//            normal fp32 samples need no row factor (rows of x wholly below 2^-128
+//            lose digits: 1.4e-3 at 2^-130), and a block with a non-finite
+//            sample gets the scale NaN.
 //
-//   scale    fp16 x_tilde only (and the fp16 copies of fp32 x): fp16 holds normal numbers from 2^-14 to 65504 only, so every
+//   scale    fp16 x_tilde only (and the fp16 copies of x in the tiled kernel):
+//            fp16 holds normal numbers from 2^-14 to 65504 only, so every
 //            activation row i is first multiplied by a power of two p_i
 //            (exact) picked from its largest magnitude a_i:
 //            a_i max(e1max, 1) p_i < 2^14.  Each x_tilde sample of the row,
@@ -495,19 +497,20 @@ __global__ __launch_bounds__(256) void expand_prefill_tiled_kernel(
 #undef SDQ_FETCH
 
 // E-stationary form of the same product, for fp16 and bf16 activations with
-// B = 128 or 256 and a single fp16 x_tilde (the layouts with Had): E^T is the
+// B = 128 or 256 and digit planes or a single fp16 x_tilde (the layouts with Had): E^T is the
 // same for every block, so a workgroup keeps one 128-sample slice of it in
 // registers, as MFMA B fragments (each wave 32 samples x B taps, hi and lo),
 // loaded once, and walks a range of (64-row tile, block) items.  Each item's
 // x tile goes straight from global memory to LDS (global_load_lds, 16-byte
 // groups XOR-swizzled by row as in the GEMM) in a ring of four buffers, the
-// next three items' copies in flight during this item's MFMAs, with the
+// next three items' copies in flight during this item's MFMAs, for fp16 x_tilde with the
 // tile's row factors p_i copied beside it.  The products run on the activation's own type: fp16 x
 // against the fp16 pair hi + lo of E, bf16 x against a bf16 pair of E formed
 // in registers (hi = bf16(E), lo = bf16(E - hi), E to ~2^-17).  E^T is the
 // A operand, so a lane's accumulators hold four consecutive samples of one
-// x_tilde row: the sums are multiplied by p_i in fp32, rounded once to fp16
-// and stored 8 bytes at a time.  Workgroups sharing an item (the slices) are
+// x_tilde row: exchanged between the halves of the wave they are one row's 32 samples,
+// written as digits (store_digits); or they are multiplied by p_i in fp32, rounded once
+// to fp16 and stored 8 bytes at a time.  Workgroups sharing an item (the slices) are
 // placed on one XCD.  Barriers are plain s_barrier with explicit counter
 // waits (a __syncthreads() fence would wait for the copies in flight).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -581,7 +584,7 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
   // Copy of item `item`'s x tile and row factors into buffer `buf`: copy j of
   // wave w writes rows TR/4 w + RPC j .. (lane l: row + l / G, slot l % G,
   // which holds group (l % G) ^ swz(row)); rows past m read row m - 1.  FC
-  // copies per wave, and one more (the factors) on wave 0.
+  // copies per wave, and for fp16 x_tilde one more (the factors; every wave its own).
   const int nb32 = static_cast<int>(nb);   // items and blocks fit 32 bits
   auto fill = [&](int buf, int64_t item) {
     const int rt = static_cast<int>(item) / nb32, b = static_cast<int>(item) - rt * nb32;
@@ -604,9 +607,10 @@ __global__ __launch_bounds__(256, 1) void expand_prefill_estat_kernel(
   // own, counted: the copies and stores issued after them stay in flight),
   // barrier, refill the buffer the previous item used with item it + NBUF - 1,
   // then the products and the stores.  Vector memory operations complete in
-  // issue order for the counter, and the counts below leave out the
-  // conditional operations (wave 0's factor copy, the padding stores), so
-  // each wait covers at least the item's own copies.
+  // issue order for the counter, and the counts below leave out what not every
+  // item issues (digit planes: the zeros past a row's end, the form word; SPI is
+  // 0 for a wave whose samples lie past M), so each wait covers at least the
+  // item's own copies.
   for (int p = 0; p < NBUF - 1; ++p) fill(p, min<int64_t>(it_begin + p, it_end - 1));
   for (int64_t it = it_begin; it < it_end; ++it) {
     const int64_t t = it - it_begin;
