@@ -502,7 +502,6 @@ __global__ __launch_bounds__(256) void unpack_base3_kernel(const uint4* __restri
                                                            int64_t nch2, int64_t nch3, int64_t quads,
                                                            int64_t total, uint4* __restrict__ fields,
                                                            float* form) {
-  if (form && blockIdx.x == 0 && threadIdx.x == 0) *form = fabsf(*form);
   // Byte -> its five codes as 2-bit fields: digit i of q is the integer part
   // of 3 r after i + 1 steps of r <- fraction part of 3 r, from r = q / 256.
   __shared__ uint32_t pat[256];
@@ -553,6 +552,7 @@ __global__ __launch_bounds__(256) void unpack_base3_kernel(const uint4* __restri
       }
     }
   }
+  if (form && blockIdx.x == 0 && threadIdx.x == 0) *form = fabsf(*form);
 }
 
 }  // namespace
