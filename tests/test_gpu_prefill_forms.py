@@ -114,3 +114,17 @@ def test_linear_runs_in_any_sufficient_workspace(levels, packing, block, osr, dt
         P.linear(x, enc, workspace=part, out=y)
         assert (torch.cuda.memory_stats()["allocation.all.allocated"] > before) == own, size
         check(y, 0)
+
+
+@CASES
+def test_noalloc_takes_the_same_form(levels, packing, block, osr, dtype):
+    # the library's own scratch, which no contraction called apart reads, holds base-3 layouts' digit
+    # planes at another place
+    torch, P, encs, x, check = _setup(levels, packing, block, osr, dtype)
+    for j in (1, 0):
+        P.sdq_prepare_layout(encs[j].layout)
+        want = P.linear(x, encs[j])
+        y = torch.full((M, encs[j].layout.n), float("nan"), device="cuda")
+        P.sdq_linear_noalloc(x, encs[j].codes, encs[j].scales, encs[j].layout, y)
+        check(y, j)
+        assert torch.equal(y, want)                        # the same plan: the scratch has room for it
