@@ -63,12 +63,12 @@ POOL_MAX = 16                    # oracle workers: the host share of one GPU
 # the probe's launches of the kernel), scaled by what the same counters read
 # for a 268,435,456-byte device copy.  Valid only for the kernel source they
 # were taken with: a source whose hash differs reports traffic null.
-TRAFFIC_FETCH_SCALE = 1.999749
+TRAFFIC_FETCH_SCALE = 1.999743
 TRAFFIC_WRITE_SCALE = 1.000000
-TRAFFIC_SOURCES = {"linear_decode.hip": "6ec58a76f52ea3de54d7702f23a1bddbec68e8a88d2b192b0f121f422201d377"}
+TRAFFIC_SOURCES = {"linear_decode.hip": "9e07b20144c653e588179dc5bd5f0a0f656dea87579d712550a3ea857f76d21b"}
 # launch family -> (source, FETCH_SIZE KiB, WRITE_SIZE KiB) per launch: the mean
 # over the 325 contraction launches of one m = 1 token step through the stack.
-TRAFFIC_KIB = {"m1_step_contractions": ("linear_decode.hip", 65091.4, 1636.6)}
+TRAFFIC_KIB = {"m1_step_contractions": ("linear_decode.hip", 65092.3, 1636.6)}
 
 
 def traffic_bytes(kernel: str):
