@@ -100,9 +100,13 @@ struct DigitParts {           // partial sums of a split contraction (splits > 1
 // tile stopped after its first eight steps: 38 us, against 8 without the code
 // loads, 9 without the copies and 17 with both through LDS) and took the
 // registers of four steps; whole calls differ by a few per cent.
+// The sums are kept 2^-kSumShift times their value, since codes times x_tilde may add
+// up past fp32 where the row scale brings the result back into it (rows of x from about
+// 2^120 on); fp32 sums lose nothing by it down to rows of 2^-126.
 // APART: a contraction called apart, which returns if fp16 x_tilde is there (a template
 // parameter, since the test in front of everything else cost a whole call 0.4 us).
 constexpr int kRing = 4;
+constexpr int kSumShift = 8;
 template <int LEVELS, int WM, int WN, int RT, int CT, int MINW, bool APART>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     const uint8_t* __restrict__ planes, LinearSet S, int64_t m, int64_t n_chunks, int64_t n_rg, int n_steps,
@@ -209,7 +213,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
     };
     i32x8 b[CT];
     auto products = [&](int pl) {
-      const int sb = (LEVELS == 3 ? 126 : 127) - 5 * pl;   // plane weight 2^-5pl, codes as 2 code
+      const int sb = (LEVELS == 3 ? 126 : 127) - 5 * pl - kSumShift;   // plane weight 2^-5pl, codes as 2 code
 #pragma unroll
       for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -270,7 +274,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
   for (int c = 0; c < CT; ++c) {
     const int64_t col = n0 + 32 * c + lane % 32;
     if (col >= n) continue;
-    const float s = LEVELS == 2 ? -scales[col] : scales[col];
+    const float s0 = LEVELS == 2 ? -scales[col] : scales[col];
+    constexpr float up = static_cast<float>(1 << kSumShift);
+    const bool small = fabsf(s0) < 0x1p100f;                 // (both products are exact)
+    const float s = small ? s0 * up : s0, back = small ? 1.0f : up;
     auto store = [&](auto whole, auto add) {
 #pragma unroll
       for (int r = 0; r < RT; ++r)
@@ -279,7 +286,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_digits_kernel(
           const int64_t row = (rg0 + wm * RT + r) * 32 + 8 * (v / 4) + 4 * half + v % 4;
           if (decltype(whole)::value || row < m) {
             float* out = y + row * n + col;
-            const float val = acc[r][c][v] * s;
+            const float val = acc[r][c][v] * back * s;
             *out = decltype(add)::value ? *out + val : val;
           }
         }

@@ -130,6 +130,32 @@ def test_nonfinite_activations_stay_in_their_rows():
     assert torch.equal(P.linear(bad, enc)[~rows], want[~rows])
 
 
+# Rows whose largest value is near the ends of fp32's normal range: below 2^-127 a block's samples are kept
+# to 2^-139 only, rms 2^-141 against 2^-128 or so of the samples (1.2e-4 more than usual, twice that of the
+# row's largest output); at 2^124 the sums of code times x_tilde, 16384 long and more, pass 2^128 before
+# the row scale brings them back.
+@pytest.mark.parametrize("levels", [2, 3])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("e", [-126, 124])
+def test_rows_at_the_ends_of_the_range(e, dtype, levels):
+    torch = require_gpu()
+    import paper_2510_03275_amd as P
+    n, k, m, block = 70, 16384, 20, 256
+    L = P.sdq_layout_init(n, k, 1.5, levels, block)
+    rng = np.random.default_rng(levels)
+    codes = rng.integers(-1, 2, size=(n, L.k_up), dtype=np.int8) if levels == 3 else \
+        (2 * rng.integers(0, 2, size=(n, L.k_up), dtype=np.int8) - 1)
+    scales = (rng.uniform(1, 2, n) * (2.0 ** -13 if e > 0 else 1.0)).astype(np.float32)
+    enc = P.Encoded(L, torch.from_numpy(LY.pack(codes, levels)).cuda(), torch.from_numpy(scales).cuda())
+    x = rng.standard_normal((m, k))
+    x, x64 = to_device_x(np.ldexp(x / np.abs(x).max(axis=1, keepdims=True), e).astype(np.float32), dtype, torch)
+    ref = OL.linear_fp64(x64, codes, scales, block, L.m_up)
+    if e > 0:
+        assert np.abs(ref / scales).max() > 2.0 ** 128       # (sums that fp32 does not hold)
+    err = OL.rel_err_rows(P.linear(x, enc).cpu().numpy().astype(np.float64), ref)
+    assert np.all(err <= TOL), err
+
+
 # more rows and columns (unsplit 32 x 256 tiles), the last column tile and row tile partial, and a group
 # of linears
 @pytest.mark.parametrize("ns,k,m,levels", [([9000], 256, 60, 3), ([6100], 512, 700, 2), ([12300], 512, 1500, 3),
