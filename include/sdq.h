@@ -292,7 +292,7 @@ size_t sdq_linear_workspace_bytes(const sdq_layout* layout, int64_t m);
  *   workspace    >= sdq_linear_workspace_bytes(layout, m) bytes, no
  *                initialisation needed.
  * Accuracy: max_r |y - y*| / max_r |y*| <= 1e-3 per activation row against the
- * fp64 definition (m > 16 on digit planes: for rows of x that reach 2^-128).  The
+ * fp64 definition (m > 16 on digit planes: for rows of x that reach 2^-126).  The
  * decode path splits K across workgroups (by k and by the panels of the whole
  * call; at 9 to 16 rows from k = 1280 on at B = 256) and then adds the partial sums
  * into y with fp32 atomics, so results may differ between calls in the last bits

@@ -14,9 +14,9 @@
 //            prefill_digits.hip (15 bits of fixed point per 32 samples, so the
 //            rounding error is below that of one fp16 rounding: rms 5e-5
 //            against 2e-4 of Gaussian samples).  E goes from -127 to 126, so
-//            normal fp32 samples need no row factor (rows of x wholly below 2^-128
-//            lose digits: 1.4e-3 at 2^-130), and a block with a non-finite
-//            sample gets the scale NaN.
+//            normal fp32 samples need no row factor (rows of x wholly below 2^-126
+//            lose digits: of the row's largest y 5e-4 there, 9e-3 at 2^-130),
+//            and a block with a non-finite sample gets the scale NaN.
 //
 //   scale    fp16 x_tilde only (and the fp16 copies of x in the tiled kernel):
 //            fp16 holds normal numbers from 2^-14 to 65504 only, so every
